@@ -114,9 +114,17 @@ typedef enum {
 
 /* How a run is driven. */
 typedef enum {
-  SP2_LAUNCH_AUTO = 0,       /* persistent for a batch of more than one
-                                instance with the Frobenius norm (Alg. 2 or
-                                SP2-ACC), otherwise a launch sequence per
+  SP2_LAUNCH_AUTO = 0,       /* the library's choice. With the Frobenius norm
+                                and kernel_config, tail_split and
+                                kernel_timing 0, a resident run where the
+                                library's cost model finds it the faster
+                                driver: one cooperative launch for the whole
+                                run (affine start, every step, the stop) in
+                                which each instance has a fixed team of
+                                workgroups, with square kernels of its own.
+                                Otherwise persistent for a batch of more than
+                                one instance with the Frobenius norm (Alg. 2
+                                or SP2-ACC), else a launch sequence per
                                 step */
   SP2_LAUNCH_SEQUENCE = 1,   /* one sequence of kernel launches per step
                                 (square kernels per configuration, then the
@@ -487,7 +495,9 @@ const char* sp2_kernel_config_name(int32_t id);
 /* The square-kernel configuration (1-based id) that instance `index` of the
  * last sp2_init_dense / sp2_batch_init uses (index 0 for a dense context),
  * as chosen by options.kernel_config, the context's kernel table or the
- * built-in default, in that order. *config_id = 0 for an instance with
+ * built-in default, in that order. A resident run (SP2_LAUNCH_AUTO) has
+ * square kernels of its own; the id is then the one that the launch
+ * sequence would use. *config_id = 0 for an instance with
  * n_occ = 0 or n (no square is computed) and for block-sparse contexts.
  * Errors: SP2_BAD_STATE before an init, SP2_INVALID_ARG. */
 sp2_status sp2_get_config(sp2_ctx ctx, int32_t index, int32_t* config_id);

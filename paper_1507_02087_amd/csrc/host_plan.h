@@ -27,4 +27,22 @@ struct Plan {
 Plan make_plan(const std::vector<int>& slots, const std::vector<int>& owner,
                const std::vector<int>& nk, int concurrency, int tail_split);
 
+// Work plan of a resident run.
+struct RunInst {
+  int64_t n = 0;
+  bool trivial = false;   // no squares: one workgroup forms the result
+};
+struct RunPlan {
+  int mb = 0;                    // tile edge / 16 (0: no plan fits)
+  std::vector<RunSeat> seats;    // one per workgroup
+  double step_us = 0.0;          // estimated time of one product
+};
+
+// Seats for every instance of the batch on a device that holds `grid`
+// workgroups of `num_cus` CUs at once (grid(mb): their number for a tile
+// edge), with the tile edge (of `edges`, ended by 0) that the cost model
+// finds fastest.
+RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edges,
+                 const std::vector<int>& grids, int num_cus);
+
 }  // namespace sp2

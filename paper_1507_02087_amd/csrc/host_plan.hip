@@ -86,4 +86,176 @@ Plan make_plan(const std::vector<int>& slots, const std::vector<int>& owner,
   return pl;
 }
 
+namespace {
+
+// Time (us) of one tile of edge 16 mb over k columns on a CU that works on
+// `share` tiles at once, and of a product's meeting: a fit to runs of N = 48
+// to 5000 at every edge, within 10 %.
+double run_tile_us(int precision, int mb, double k, double share) {
+  // flops / us of a CU's matrix cores, by precision and edge
+  static const double rate[3][6] = {{0, 0, 0.272e6, 0.272e6, 0.272e6, 0},
+                                    {0, 0, 0.55e6, 0.55e6, 0.55e6, 0.55e6},
+                                    {0, 0, 0.95e6, 0, 1.56e6, 0}};
+  // reduction, epilogue and store of a tile
+  static const double epi[3][6] = {{0, 0, 4.4, 6.3, 5.5, 0},
+                                   {0, 0, 3.3, 5.4, 7.0, 10.0},
+                                   {0, 0, 3.2, 0, 7.0, 0}};
+  const double bm = 16.0 * mb;
+  return share * (2.0 * bm * bm * k / rate[precision][mb] + epi[precision][mb]);
+}
+constexpr double kRunMeetUs = 8.0;
+
+}  // namespace
+
+RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edges,
+                 const std::vector<int>& grids, int num_cus) {
+  const int count = static_cast<int>(inst.size());
+  RunPlan best;
+  std::vector<int> best_size;
+  int best_cap = 0;
+  for (int q = 0; edges[q]; ++q) {
+    // a single run in FP32 or BF16x3 takes one workgroup per CU: its four
+    // waves alone keep the matrix cores busy, and a second workgroup only
+    // gets in their way (FP32, N = 4000, 48-tiles: 553 us a step against
+    // 585). In FP64 a second one hides the first's epilogue (N = 4000,
+    // 64-tiles: 966 us against 1023), and the instances of a batch hide each
+    // other's waits.
+    const int mb = edges[q], bm = 16 * mb;
+    const int cap =
+        (count == 1 && precision != 0) ? std::min(grids[q], num_cus) : grids[q];
+    if (cap < count) continue;
+    std::vector<int64_t> tiles(count);
+    std::vector<double> tile_us(count);
+    int64_t total = 0;
+    for (int b = 0; b < count; ++b) {
+      const int64_t nt = (inst[b].n + bm - 1) / bm;
+      tiles[b] = inst[b].trivial ? 1 : nt * (nt + 1) / 2;
+      total += tiles[b];
+    }
+    if (count == 1) {
+      const double us = run_tile_us(precision, mb, static_cast<double>(inst[0].n), 1.0) *
+                        static_cast<double>((total + num_cus - 1) / num_cus);
+      if (best.mb == 0 || us + kRunMeetUs < best.step_us) {
+        best.mb = mb;
+        best_cap = cap;
+        best.step_us = us + kRunMeetUs;
+        best_size.assign(1, static_cast<int>(std::min<int64_t>(total, cap)));
+      }
+      continue;
+    }
+    // how many tiles a CU works on at once
+    const double share = std::min<double>(
+        std::max(1.0, static_cast<double>(total) / num_cus), static_cast<double>(cap) / num_cus);
+    double lo = 0.0, hi = 0.0;
+    for (int b = 0; b < count; ++b) {
+      tile_us[b] = inst[b].trivial
+                       ? 1.0
+                       : run_tile_us(precision, mb, static_cast<double>(inst[b].n), share);
+      hi = std::max(hi, tile_us[b] * static_cast<double>(tiles[b]));
+    }
+    // smallest step time whose teams fit: a team of ceil(tiles / rounds)
+    auto seats_for = [&](double us, std::vector<int>* size) {
+      int64_t s = 0;
+      for (int b = 0; b < count; ++b) {
+        const int64_t rounds = static_cast<int64_t>(us / tile_us[b]);
+        if (rounds < 1) return static_cast<int64_t>(cap) + 1;
+        const int64_t g = (tiles[b] + rounds - 1) / rounds;
+        if (size) (*size)[b] = static_cast<int>(g);
+        s += g;
+      }
+      return s;
+    };
+    hi *= 1.0001;
+    if (seats_for(hi, nullptr) > cap) continue;
+    double work = 0.0;
+    for (int b = 0; b < count; ++b) work += tile_us[b] * static_cast<double>(tiles[b]);
+    for (int it = 0; it < 40; ++it) {
+      const double mid = 0.5 * (lo + hi);
+      (seats_for(mid, nullptr) <= cap ? hi : lo) = mid;
+    }
+    // Teams are fixed, so a batch whose largest instances get too few seats
+    // leaves most of the device idle; the queue of the persistent driver
+    // deals its tiles out instead (512 FP32 instances of 64 to 1024 rows on
+    // 512 seats: 152 ms against 67). Its step costs the instances' share of
+    // the device and some 30 us of waiting and publishing.
+    if (hi + kRunMeetUs > 1.3 * work / cap + 30.0) continue;
+    if (best.mb == 0 || hi + kRunMeetUs < best.step_us) {
+      best.mb = mb;
+      best_cap = cap;
+      best.step_us = hi + kRunMeetUs;
+      best_size.assign(count, 0);
+      seats_for(hi, &best_size);
+    }
+  }
+  if (best.mb == 0) return best;
+  // Workgroup b runs on XCD b mod 8: a team of up to 32 workgroups (the CUs
+  // of an XCD) goes to the least loaded XCD, whose L2 then serves all its
+  // exchanges; a larger one is dealt in eight contiguous parts, so that
+  // neighbouring tiles share their panels' XCD.
+  const int X = 8;
+  std::vector<int> order(count);
+  for (int b = 0; b < count; ++b) order[b] = b;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return best_size[a] > best_size[b]; });
+  std::vector<std::vector<RunSeat>> col(X);
+  std::vector<int> base(count, 0);
+  int next = 0;
+  for (int b = 0; b < count; ++b) {
+    base[b] = next;
+    next += best_size[b];
+  }
+  auto least = [&]() {
+    int x = 0;
+    for (int y = 1; y < X; ++y)
+      if (col[y].size() < col[x].size()) x = y;
+    return x;
+  };
+  int total = 0;
+  for (int s : best_size) total += s;
+  const size_t rows = static_cast<size_t>((total + X - 1) / X);
+  for (int b : order) {
+    const int size = best_size[b];
+    const int x = least();
+    const bool fits = (count == 1) ? size * X <= best_cap : col[x].size() + size <= rows;
+    if (size <= 32 && fits) {
+      for (int r = 0; r < size; ++r) col[x].push_back(RunSeat{b, r, size, base[b], 0});
+    } else {
+      int r = 0;
+      for (int y = 0; y < X; ++y) {
+        const int part = (size - r + X - y - 1) / (X - y);
+        for (int k = 0; k < part && col[y].size() < rows; ++k)
+          col[y].push_back(RunSeat{b, r++, size, base[b], 0});
+      }
+      while (r < size) col[least()].push_back(RunSeat{b, r++, size, base[b], 0});
+    }
+  }
+  size_t depth = 0;
+  for (const auto& c : col) depth = std::max(depth, c.size());
+  best.seats.assign(depth * X, RunSeat{0, 0, 0, 0, 0});
+  for (int x = 0; x < X; ++x)
+    for (size_t k = 0; k < col[x].size(); ++k) best.seats[k * X + x] = col[x][k];
+  // The last round's tiles go to the seats of the lowest rows of the grid
+  // (row k of an XCD's column is its k-th workgroup, so the first rows are
+  // the first workgroups of its CUs), numbered XCD by XCD. Dealt by rank,
+  // they would all fall on the CUs of the first XCDs.
+  std::vector<int64_t> rem(count), given(count, 0), number(count);
+  for (int b = 0; b < count; ++b) {
+    const int64_t nt = (inst[b].n + 16 * best.mb - 1) / (16 * best.mb);
+    const int64_t tiles = inst[b].trivial ? 0 : nt * (nt + 1) / 2;
+    rem[b] = tiles % best_size[b];
+    number[b] = tiles - rem[b];
+  }
+  const int none = INT32_MAX;
+  for (RunSeat& s : best.seats) {
+    if (s.size == 0) continue;
+    s.last = (given[s.inst]++ < rem[s.inst]) ? 0 : none;
+  }
+  for (int x = 0; x < X; ++x)
+    for (size_t k = 0; k < depth; ++k) {
+      RunSeat& s = best.seats[k * X + x];
+      if (s.size > 0 && s.last != none) s.last = static_cast<int32_t>(number[s.inst]++);
+    }
+  return best;
+}
+
 }  // namespace sp2

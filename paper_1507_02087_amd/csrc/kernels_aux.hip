@@ -56,8 +56,9 @@ __global__ __launch_bounds__(kThreads) void state_reset_kernel(
     me->alpha[0] = 1.0;
     if (blockIdx.x == 0) *ndone = 0;
   }
-  if (blockIdx.x == 0 && zero)
-    for (int i = threadIdx.x; i < nzero; i += kThreads) zero[i] = 0;
+  if (zero)
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < nzero; i += gridDim.x * kThreads)
+      zero[i] = 0;
 }
 
 // X_0 = (lambda_max I - F) / (lambda_max - lambda_min) in FP64 (Alg. 2),
@@ -317,6 +318,51 @@ __global__ __launch_bounds__(kThreads) void copy_out_sym_kernel(
   }
 }
 
+// The same from an iterate in operand order: block (bi, bj) of 32 x 32 is
+// read as whole operand blocks (contiguous kilobytes) into LDS and written
+// as rows. With kSym only blocks bi <= bj are read, and each is also written
+// transposed.
+template <typename Tin, typename Tout, bool kSym>
+__global__ __launch_bounds__(kThreads) void copy_out_op_kernel(
+    const Tin* __restrict__ X, int n, int ldx, OpMap m, Tout* __restrict__ D,
+    int64_t ldd) {
+  constexpr int B = 32, V = 16 / sizeof(Tin), KC = 64 / sizeof(Tin), NC = B / KC;
+  typedef Tin vec __attribute__((ext_vector_type(V)));
+  __shared__ Tin t[B][B + 1];
+  const int bi = blockIdx.y, bj = blockIdx.x;
+  if (kSym && bi > bj) return;
+  const int i0 = bi * B, j0 = bj * B;
+  for (int v = threadIdx.x; v < B * B / V; v += kThreads) {
+    const int blk = v / 64, l = v % 64;
+    const int r = 16 * (blk / NC) + (l & 15), c = KC * (blk % NC) + V * (l >> 4);
+    // the matrix is padded to whole operand blocks, not to whole 32-blocks
+    if (i0 + r < n && j0 + c < n) {
+      const vec x = *reinterpret_cast<const vec*>(X + op_off<Tin>(i0 + r, j0 + c, ldx));
+#pragma unroll
+      for (int e = 0; e < V; ++e) t[r][c + e] = x[e];
+    }
+  }
+  __syncthreads();
+  auto val = [&](Tin x, bool diag) {
+    return static_cast<Tout>((static_cast<double>(x) - (diag ? m.c : 0.0)) / m.a);
+  };
+  for (int e = threadIdx.x; e < B * B; e += kThreads) {
+    const int r = e / B, c = e % B;
+    const int i = i0 + r, j = j0 + c;
+    if (i < n && j < n) {
+      const Tin x = (kSym && bi == bj && r > c) ? t[c][r] : t[r][c];
+      D[static_cast<int64_t>(i) * ldd + j] = val(x, i == j);
+    }
+  }
+  if (!kSym || bi == bj) return;
+  for (int e = threadIdx.x; e < B * B; e += kThreads) {
+    const int r = e / B, c = e % B;
+    const int i = j0 + r, j = i0 + c;
+    if (i < n && j < n)
+      D[static_cast<int64_t>(i) * ldd + j] = val(t[c][r], false);
+  }
+}
+
 int grid_for(int64_t total) {
   int64_t g = (total + kThreads - 1) / kThreads;
   if (g > 8192) g = 8192;
@@ -351,6 +397,29 @@ hipError_t launch_finalize(const Instance* inst, int count,
   hipLaunchKernelGGL(finalize_kernel, dim3(count), dim3(kThreads), 0, s, inst,
                      count, part, part_f0, ndone, mirror, iter);
   return hipGetLastError();
+}
+
+namespace {
+template <typename Tin, typename Tout>
+hipError_t copy_out_op(const void* X, int n, int ldx, void* D, int64_t ldd, bool symmetric,
+                       OpMap m, hipStream_t s) {
+  const int nb = (n + 31) / 32;
+  if (symmetric)
+    hipLaunchKernelGGL((copy_out_op_kernel<Tin, Tout, true>), dim3(nb, nb), dim3(kThreads), 0,
+                       s, static_cast<const Tin*>(X), n, ldx, m, static_cast<Tout*>(D), ldd);
+  else
+    hipLaunchKernelGGL((copy_out_op_kernel<Tin, Tout, false>), dim3(nb, nb), dim3(kThreads), 0,
+                       s, static_cast<const Tin*>(X), n, ldx, m, static_cast<Tout*>(D), ldd);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_copy_out_op(const void* X, bool fp64_store, int n, int ldx, void* D,
+                              int64_t ldd, bool out_fp64, bool symmetric, OpMap m,
+                              hipStream_t s) {
+  if (fp64_store) return copy_out_op<double, double>(X, n, ldx, D, ldd, symmetric, m, s);
+  if (out_fp64) return copy_out_op<float, double>(X, n, ldx, D, ldd, symmetric, m, s);
+  return copy_out_op<float, float>(X, n, ldx, D, ldd, symmetric, m, s);
 }
 
 hipError_t launch_copy_out(const void* X, bool fp64_store, int n, int ldx,

@@ -8,7 +8,8 @@
 // configuration. The polynomial choices, the stop tests and the outcomes
 // live in device memory (one DevState per instance); the finalize kernel
 // counts stopped instances and tells the host, through host-coherent pinned
-// memory, when all have stopped. The host keeps up to kLookahead steps
+// memory, when all have stopped. (A resident run is one cooperative launch
+// instead, see run_impl.h.) The host keeps up to kLookahead steps
 // queued ahead of the step whose outcome it last observed, so the device
 // never waits on the host; steps queued after the stop return at once
 // because every kernel first reads its instance's done flag.
@@ -182,6 +183,21 @@ struct sp2_ctx_s {
   long long wall_khz = 100000;     // rate of the kernels' constant clock
   long long wait_ms = 2000;        // longest wait of a workgroup for an item
 
+  // resident run (one cooperative launch): the tile edge / 16, the seats of
+  // its workgroups, and the pinned host copy of the states
+  bool resident = false;
+  int run_mb = 0;
+  int run_grid = 0;
+  void* d_run = nullptr;           // instances, tiles and seats
+  size_t d_run_cap = 0;
+  const sp2::RunSeat* d_seats = nullptr;
+  const int2* d_run_tiles = nullptr;
+  const Instance* d_run_inst = nullptr;
+  std::vector<int> run_grids[3][2];   // co-resident workgroups per edge, by
+                                      // precision and McWeeny; found once
+  DevState* h_state = nullptr;     // pinned
+  size_t h_state_cap = 0;
+
   // Workspace arena of the no-allocation entry point (null for contexts made
   // by sp2_create): every workspace is carved from it instead of allocated.
   char* arena = nullptr;
@@ -256,6 +272,15 @@ int default_config(int precision, int64_t n) {
     case SP2_FP32: return n >= 1024 ? 4 : 3;
     default: return n >= 6144 ? 13 : 11;
   }
+}
+
+// The square-kernel configuration of an instance of dimension n: the one the
+// options name, else the context's table, else the built-in choice.
+int library_config(sp2_ctx c, int64_t n) {
+  if (c->opt.kernel_config) return c->opt.kernel_config - 1;
+  for (const auto& e : c->table)
+    if (e.precision == c->opt.precision && n <= e.n_max) return e.cfg;
+  return default_config(c->opt.precision, n);
 }
 
 sp2_status ensure_events(sp2_ctx c) {
@@ -333,6 +358,135 @@ void release_groups(sp2_ctx c) {
   c->groups.clear();
 }
 
+// Co-resident workgroups of the resident run for every tile edge of the
+// context's precision.
+const std::vector<int>& run_grids(sp2_ctx c, bool mw) {
+  std::vector<int>& g = c->run_grids[c->opt.precision][mw ? 1 : 0];
+  if (g.empty())
+    for (const int* e = sp2::run_edges(c->opt.precision); *e; ++e)
+      g.push_back(sp2::run_max_grid(c->opt.precision, *e, mw, c->num_cus));
+  return g;
+}
+
+// Words of a resident run's exchange, cleared before it: the error word and
+// a line per instance's release word, then the seats' posts.
+size_t run_sync_words(int count, size_t seats) {
+  return 32 * (static_cast<size_t>(count) + 1) +
+         seats * (sizeof(sp2::RunPost) / sizeof(int32_t));
+}
+
+// Whether a resident run is the better driver, and its plan.
+bool choose_resident(sp2_ctx c, sp2::RunPlan* plan) {
+  const sp2_options& o = c->opt;
+  if (c->arena || o.launch != SP2_LAUNCH_AUTO || o.norm != SP2_NORM_FROBENIUS ||
+      o.kernel_config != 0 || o.tail_split != 0 || o.kernel_timing != 0)
+    return false;
+  // Sizes where it is: measured against the launch sequence, the resident
+  // step is the faster one at every N up to these (FP64 8192: equal; FP32
+  // 6144: 1853 us a step against 1892; BF16x3 3500: 188 against 199, 4096:
+  // equal, 5600: 742 against 510, where the sequence's 256-tiles take over).
+  const int64_t most = (o.precision == SP2_BF16X3) ? 3584 : 6144;
+  std::vector<sp2::RunInst> inst;
+  for (const HostInst& h : c->hi)
+    if (h.n > most) return false;
+  for (const HostInst& h : c->hi) inst.push_back(sp2::RunInst{h.n, h.n_occ == 0 || h.n_occ == h.n});
+  // a McWeeny run uses the same plan, so both kernels have to fit
+  std::vector<int> g = run_grids(c, false);
+  const std::vector<int>& gm = run_grids(c, true);
+  for (size_t q = 0; q < g.size(); ++q) g[q] = std::min(g[q], gm[q]);
+  *plan = sp2::plan_run(inst, o.precision, sp2::run_edges(o.precision), g, c->num_cus);
+  return plan->mb != 0;
+}
+
+// Prepares a resident run: iterates in operand order, and one upload of the
+// instance table, the tiles and the seats.
+sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
+  const int count = static_cast<int>(c->hi.size());
+  const size_t esz = c->fp64_store ? 8 : 4;
+  hipStream_t s = c->stream;
+  const int bm = 16 * plan.mb;
+  size_t pool_elems = 0;
+  for (HostInst& h : c->hi) {
+    h.cfg = library_config(c, h.n);
+    h.np = ((h.n + bm - 1) / bm) * bm;
+    h.ld = h.np;
+    h.xoff = pool_elems;
+    pool_elems += static_cast<size_t>(h.np) * h.ld;   // a multiple of 256
+    h.trivial = (h.n_occ == 0 || h.n_occ == h.n);
+  }
+  for (int q = 0; q < 2; ++q)
+    SP2_HIP(c, grow(c, c->pool[q], c->pool_cap[q], pool_elems * esz, s));
+  const bool split = (c->opt.precision == SP2_BF16X3);
+  if (split)
+    for (int q = 0; q < 4; ++q)
+      SP2_HIP(c, grow(c, c->split_pool[q], c->split_cap[q], pool_elems * 2, s));
+  // behind the states: the error word (one copy brings both), the teams'
+  // release words, the posts of the seats and the coefficients
+  SP2_HIP(c, grow(c, c->d_st, c->d_st_cap,
+                  count * sizeof(DevState) +
+                      run_sync_words(count, plan.seats.size()) * sizeof(int32_t) +
+                      count * 8 * sizeof(double), s));
+  std::vector<int2> tiles;
+  std::vector<Instance> inst(count);
+  for (int b = 0; b < count; ++b) {
+    const HostInst& h = c->hi[b];
+    Instance& in = inst[b];
+    in = Instance{};
+    in.X[0] = static_cast<char*>(c->pool[0]) + h.xoff * esz;
+    in.X[1] = static_cast<char*>(c->pool[1]) + h.xoff * esz;
+    for (int q = 0; q < 2 && split; ++q) {
+      in.XH[q] = static_cast<char*>(c->split_pool[2 * q]) + h.xoff * 2;
+      in.XL[q] = static_cast<char*>(c->split_pool[2 * q + 1]) + h.xoff * 2;
+    }
+    in.F = h.F;
+    in.ldf = h.ldf;
+    in.n = static_cast<int>(h.n);
+    in.ld = static_cast<int>(h.ld);
+    in.tile0 = static_cast<int>(tiles.size());
+    append_tile_list(static_cast<int>(h.np / bm), tiles);
+    in.ntiles = static_cast<int>(tiles.size()) - in.tile0;
+    in.st = c->d_st + b;
+    in.lmax = h.lmax;
+    in.width = h.lmax - h.lmin;
+    in.tau = c->opt.trunc_tau;
+    in.prm.n_occ = static_cast<double>(h.n_occ);
+    in.prm.n = static_cast<double>(h.n);
+    in.prm.branch = c->opt.branch;
+    in.prm.max_iter = c->opt.max_iter;
+    in.prm.norm = c->opt.norm;
+  }
+  const size_t ib = (count * sizeof(Instance) + 255) / 256 * 256;
+  const size_t sb = (plan.seats.size() * sizeof(sp2::RunSeat) + 255) / 256 * 256;
+  std::vector<char> blob(ib + sb + tiles.size() * sizeof(int2));
+  memcpy(blob.data(), inst.data(), count * sizeof(Instance));
+  memcpy(blob.data() + ib, plan.seats.data(), plan.seats.size() * sizeof(sp2::RunSeat));
+  memcpy(blob.data() + ib + sb, tiles.data(), tiles.size() * sizeof(int2));
+  SP2_HIP(c, grow(c, c->d_run, c->d_run_cap, blob.size(), s));
+  SP2_HIP(c, hipMemcpyAsync(c->d_run, blob.data(), blob.size(), hipMemcpyHostToDevice, s));
+  SP2_HIP(c, hipStreamSynchronize(s));
+  const char* base = static_cast<const char*>(c->d_run);
+  c->d_run_inst = reinterpret_cast<const Instance*>(base);
+  c->d_seats = reinterpret_cast<const sp2::RunSeat*>(base + ib);
+  c->d_run_tiles = reinterpret_cast<const int2*>(base + ib + sb);
+  c->run_mb = plan.mb;
+  c->run_grid = static_cast<int>(plan.seats.size());
+  const size_t hb = count * sizeof(DevState) + 256;
+  if (hb > c->h_state_cap) {
+    if (c->h_state) (void)hipHostFree(c->h_state);
+    c->h_state = nullptr;
+    c->h_state_cap = 0;
+    SP2_HIP(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_state), hb, hipHostMallocDefault));
+    c->h_state_cap = hb;
+  }
+  c->h_inst = inst;
+  c->mcweeny = false;
+  c->stretch = false;
+  c->persistent = false;
+  c->spec_nchunks = 0;
+  release_groups(c);
+  return SP2_OK;
+}
+
 // Builds the instance table, tile table, launch groups and their plans, and
 // (re)allocates every workspace. Instances come in c->hi.
 sp2_status setup(sp2_ctx c) {
@@ -340,18 +494,11 @@ sp2_status setup(sp2_ctx c) {
   const size_t esz = c->fp64_store ? 8 : 4;
   hipStream_t s = c->stream;
   release_graph(c);
+  sp2::RunPlan plan;
+  c->resident = choose_resident(c, &plan);
+  if (c->resident) return setup_resident(c, plan);
   // configurations, padding, pool offsets
-  auto choose = [&](int64_t n) {
-    int cfg = c->opt.kernel_config ? c->opt.kernel_config - 1
-                                   : default_config(c->opt.precision, n);
-    if (!c->opt.kernel_config)
-      for (const auto& e : c->table)
-        if (e.precision == c->opt.precision && n <= e.n_max) {
-          cfg = e.cfg;
-          break;
-        }
-    return cfg;
-  };
+  auto choose = [&](int64_t n) { return library_config(c, n); };
   // the persistent driver runs every instance with one configuration: the
   // choice for the largest instance when the persistent kernel is compiled
   // for it, else the 64/128-tile default of the precision
@@ -693,12 +840,72 @@ sp2_status run_persistent(sp2_ctx c) {
   return SP2_OK;
 }
 
+// FP64 resident runs past this N add up a wave's K part (a quarter of the K
+// range) as one chain, without a second set of sums: the launch sequence
+// adds the whole range as one chain there, so the result is still the more
+// accurate one (N = 4096: 5.0e-15 against 8.5e-15), and rounding further
+// below the resolution of the traces only delays the stop (ten runs at
+// N = 3001: 303 steps with the second set, 292 without, 291 in sequence).
+constexpr int kRunChainN = 1800;
+
+// One resident run: state reset, the cooperative launch, and the copy of the
+// states and the error word.
+sp2_status run_resident(sp2_ctx c) {
+  const int count = static_cast<int>(c->hi.size());
+  hipStream_t s = c->stream;
+  int32_t* const err = reinterpret_cast<int32_t*>(c->d_st + count);
+  sp2::RunArgs a{};
+  a.inst = c->d_run_inst;
+  a.seats = c->d_seats;
+  a.tiles = c->d_run_tiles;
+  a.err = err;
+  a.flag = err + 32;
+  a.post = reinterpret_cast<sp2::RunPost*>(a.flag + 32 * count);
+  const size_t words = run_sync_words(count, c->run_grid);
+  a.coef = reinterpret_cast<double*>(err + words);
+  a.ndone = c->d_ndone;
+  a.count = count;
+  a.stretch = c->stretch ? 1 : 0;
+  a.chain_n = kRunChainN;
+  a.wait_limit = c->wait_ms * c->wall_khz;
+  c->timed = false;
+  c->square_ms.clear();
+  c->norm_ms.clear();
+  SP2_HIP(c, hipEventRecord(c->ev_start, s));
+  SP2_HIP(c, sp2::launch_state_reset(c->d_st, count, c->d_ndone, err,
+                                     static_cast<int>(words), s));
+  SP2_HIP(c, sp2::launch_run(c->opt.precision, c->run_mb, c->mcweeny, a, c->run_grid, s));
+  SP2_HIP(c, hipEventRecord(c->ev_stop, s));
+  SP2_HIP(c, hipMemcpyAsync(c->h_state, c->d_st,
+                            count * sizeof(DevState) + sizeof(int32_t),
+                            hipMemcpyDeviceToHost, s));
+  SP2_HIP(c, hipStreamSynchronize(s));
+  float ms = 0.f;
+  SP2_HIP(c, hipEventElapsedTime(&ms, c->ev_start, c->ev_stop));
+  if (*reinterpret_cast<const int32_t*>(c->h_state + count) != 0)
+    return fail(c, SP2_HIP_ERROR,
+                "resident run: a workgroup waited for its team longer than "
+                "its limit", hipSuccess);
+  c->host_state.assign(c->h_state, c->h_state + count);
+  int32_t steps = 0;
+  for (const DevState& h : c->host_state) {
+    if (!h.done)
+      return fail(c, SP2_BAD_STATE, "run ended without an outcome", hipSuccess);
+    steps = std::max(steps, h.squares);
+  }
+  c->steps = steps;
+  c->run_ms = ms;
+  c->ran = true;
+  return SP2_OK;
+}
+
 // Steps enqueued between two looks at the done counter by a context of the
 // no-allocation entry point (it has no pinned mirror and no events).
 constexpr int kNoAllocChunk = 4;
 
 sp2_status run_batch(sp2_ctx c) {
   SP2_HIP(c, hipSetDevice(c->device));
+  if (c->resident && !c->bsr) return run_resident(c);
   if (c->persistent && !c->mcweeny && !c->bsr) return run_persistent(c);
   hipStream_t s = c->stream;
   const int count = static_cast<int>(c->hi.size());
@@ -928,6 +1135,15 @@ sp2_status copy_density(sp2_ctx c, int idx, void* D_dev, int64_t ldd,
   const size_t esz = c->fp64_store ? 8 : 4;
   const void* X = static_cast<const char*>(c->pool[st.n & 1]) + h.xoff * esz;
   SP2_HIP(c, hipSetDevice(c->device));
+  if (c->resident) {
+    // every iterate but X_0 is symmetric (and the lower triangle of the
+    // BF16x3 ones is not stored)
+    SP2_HIP(c, sp2::launch_copy_out_op(X, c->fp64_store, static_cast<int>(h.n),
+                                       static_cast<int>(h.ld), D_dev, ldd, as_fp64 != 0,
+                                       st.n > 0, result_map(c, idx), c->stream));
+    SP2_HIP(c, hipStreamSynchronize(c->stream));
+    return SP2_OK;
+  }
   // configurations with presplit operands leave the FP32 iterate's lower
   // triangle unwritten unless the spectral norm reads it
   const bool sym = sp2::kernel_config(h.cfg)->presplit &&
@@ -1129,10 +1345,12 @@ sp2_status sp2_destroy(sp2_ctx c) {
   rel(c->d_pitems);
   rel(c->d_pctl);
   rel(c->d_pcnt);
+  rel(c->d_run);
   release_graph(c);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   release_groups(c);
   if (c->mirror) (void)hipHostFree(c->mirror);
+  if (c->h_state) (void)hipHostFree(c->h_state);
   if (c->ev_start) (void)hipEventDestroy(c->ev_start);
   if (c->ev_stop) (void)hipEventDestroy(c->ev_stop);
   for (hipEvent_t e : c->ev_ring)
@@ -1418,6 +1636,7 @@ sp2_status sp2_init_bsr(sp2_ctx c, int64_t n, int32_t block, int64_t nnzb,
   c->opt = opt;
   c->fp64_store = false;
   c->bsr = true;
+  c->resident = false;
   c->inited = true;
   return SP2_OK;
 }
@@ -1638,8 +1857,9 @@ sp2_status sp2_set_mcweeny(sp2_ctx c, int32_t count, const double* mu,
     in.sched_alpha = static_cast<const double*>(c->d_sched) +
                      static_cast<size_t>(b) * L;
   }
-  SP2_HIP(c, hipMemcpyAsync(c->d_inst, c->h_inst.data(),
-                            count * sizeof(Instance), hipMemcpyHostToDevice, s));
+  SP2_HIP(c, hipMemcpyAsync(c->resident ? c->d_run : static_cast<void*>(c->d_inst),
+                            c->h_inst.data(), count * sizeof(Instance),
+                            hipMemcpyHostToDevice, s));
   SP2_HIP(c, hipStreamSynchronize(s));
   c->mcweeny = true;
   return SP2_OK;
@@ -1733,8 +1953,9 @@ sp2_status sp2_set_homo_lumo(sp2_ctx c, int32_t count, const double* homo_out,
     in.sched_alpha = nmax[b] ? d_alpha + static_cast<size_t>(b) * L : nullptr;
     in.sched_p = nmax[b] ? d_pol + static_cast<size_t>(b) * L : nullptr;
   }
-  SP2_HIP(c, hipMemcpyAsync(c->d_inst, c->h_inst.data(),
-                            count * sizeof(Instance), hipMemcpyHostToDevice, s));
+  SP2_HIP(c, hipMemcpyAsync(c->resident ? c->d_run : static_cast<void*>(c->d_inst),
+                            c->h_inst.data(), count * sizeof(Instance),
+                            hipMemcpyHostToDevice, s));
   // the copies read host vectors that go out of scope
   SP2_HIP(c, hipStreamSynchronize(s));
   return SP2_OK;

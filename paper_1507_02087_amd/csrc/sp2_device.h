@@ -335,6 +335,59 @@ hipError_t launch_persist_seed(const Instance* inst, int count, const PQueue& q,
 hipError_t launch_persist(int cfg, const SquareArgs& a, const PQueue& q,
                           int grid, hipStream_t s);
 
+// Offset of element (row, col) of a matrix in operand order, the storage of
+// resident runs: blocks of 16 rows by 64 bytes (KC columns), lane l of a wave
+// holding the 16 bytes at row l % 16, column group l / 16. ld is a multiple
+// of KC.
+template <typename E>
+__host__ __device__ __forceinline__ size_t op_off(int row, int col, int ld) {
+  constexpr int KC = 64 / sizeof(E), V = 16 / sizeof(E);
+  return (static_cast<size_t>(row >> 4) * (ld / KC) + col / KC) * (16 * KC) +
+         ((row & 15) + 16 * ((col % KC) / V)) * V + col % V;
+}
+
+// Resident runs: one cooperative launch for a whole run. Each workgroup has
+// a seat: its instance, its rank in the instance's team, the team's size
+// (0: the seat is empty), the team's first slot in the partial sums, and the
+// seat's tile in the last round when size does not divide the tiles (a tile
+// index past the last: none). The seats that have one are spread evenly over
+// the CUs.
+struct RunSeat {
+  int32_t inst, rank, size, base, last;
+};
+// What a seat posts once per product: its partial sums and the phase.
+struct RunPost {
+  double sum[3];
+  int32_t phase, pad;
+};
+struct RunArgs {
+  const Instance* inst;
+  const RunSeat* seats;
+  const int2* tiles;
+  RunPost* post;          // per seat, phase 0 at launch
+  int32_t* flag;          // per instance 32 words, [0] zero at launch: the
+                          // word that releases the team
+  double* coef;           // per instance 8: StepCoef of the next product
+  int32_t* ndone;
+  int32_t* err;           // nonzero once a wait exceeded its limit
+  int32_t count;          // instances
+  int32_t stretch;        // the run stretches the matrices it squares
+  int32_t chain_n;        // FP64: N past which a wave's K part is one chain
+  long long wait_limit;   // constant-clock ticks of a team's longest wait
+};
+// Tile edges, in units of 16 rows, that a precision's resident run is
+// compiled for, smallest first, ended by 0.
+const int* run_edges(int precision);
+// Workgroups of the resident run that fit on the device at once (0: none).
+int run_max_grid(int precision, int mb, bool mw, int num_cus);
+hipError_t launch_run(int precision, int mb, bool mw, const RunArgs& a, int grid,
+                      hipStream_t s);
+// D = (X - c I) / a from an iterate in operand order; `symmetric` reads the
+// upper triangle only.
+hipError_t launch_copy_out_op(const void* X, bool fp64_store, int n, int ldx,
+                              void* D, int64_t ldd, bool out_fp64, bool symmetric,
+                              OpMap m, hipStream_t s);
+
 // Arguments of one spectral-norm launch: every running instance with a
 // chunk table entry (instance, first row) per kSpecRows rows.
 struct SpecArgs {
