@@ -123,6 +123,13 @@ struct sp2_ctx_s {
   int spec_nchunks = 0;
   int spec_grid = 0;
   int spec_vec_cap = 0;
+  // spectral norm of a single dense instance from registers: the launch's
+  // workgroups (0: the chunked kernel), its control words and vectors
+  int spec_run_grid = 0;
+  int32_t* d_spec_run_ctl = nullptr;
+  size_t d_spec_run_ctl_cap = 0;
+  double* d_spec_run = nullptr;
+  size_t d_spec_run_cap = 0;
   DevState* d_st = nullptr;
   size_t d_st_cap = 0;
   int2* d_tiles = nullptr;
@@ -375,6 +382,13 @@ size_t run_sync_words(int count, size_t seats) {
          seats * (sizeof(sp2::RunPost) / sizeof(int32_t));
 }
 
+// Instances that compute squares.
+int active_instances(sp2_ctx c) {
+  int active = 0;
+  for (const HostInst& h : c->hi) active += h.trivial ? 0 : 1;
+  return active;
+}
+
 // Whether a resident run is the better driver, and its plan.
 bool choose_resident(sp2_ctx c, sp2::RunPlan* plan) {
   const sp2_options& o = c->opt;
@@ -600,6 +614,20 @@ sp2_status setup(sp2_ctx c) {
     c->spec_grid = std::min<int>(gmax, static_cast<int>(chunks.size()) + active);
   }
   c->spec_nchunks = static_cast<int>(chunks.size());
+  // a single instance whose iterate fits the registers of the CUs (FP32 to
+  // N = 4080, FP64 to 2816): a Lanczos step at N = 4000 takes 21 us from
+  // there and 67 in chunks read from memory
+  c->spec_run_grid = 0;
+  if (spectral && count == 1 && active_instances(c) == 1) {
+    c->spec_run_grid = sp2::spectral_resident_grid(
+        c->fp64_store, static_cast<int>(c->hi[0].n), c->num_cus);
+    if (c->spec_run_grid > 0) {
+      SP2_HIP(c, grow(c, c->d_spec_run_ctl, c->d_spec_run_ctl_cap,
+                      (sp2::kSpecRunCtl + c->num_cus) * sizeof(int32_t), s));
+      SP2_HIP(c, grow(c, c->d_spec_run, c->d_spec_run_cap,
+                      (4 * sp2::kSpecRunMax + 2 * sp2::kLanczosMax) * sizeof(double), s));
+    }
+  }
 
   // instance table, tiles and affine-start blocks
   SP2_HIP(c, grow(c, c->d_st, c->d_st_cap, count * sizeof(DevState), s));
@@ -929,9 +957,13 @@ sp2_status run_batch(sp2_ctx c) {
     c->ev_nm.assign(2 * (SP2_MAX_ITER_LIMIT + 1), nullptr);
     for (hipEvent_t& e : c->ev_nm) SP2_HIP(c, hipEventCreate(&e));
   }
-  SP2_HIP(c, sp2::launch_state_reset(c->d_st, count, c->d_ndone,
-                                     spectral ? c->d_spec_ctl : nullptr,
-                                     (sp2::kMaxIter + 2) * sp2::kSpecCtl, s));
+  const bool spec_run = spectral && !c->bsr && c->spec_run_grid > 0;
+  SP2_HIP(c, sp2::launch_state_reset(
+                 c->d_st, count, c->d_ndone,
+                 spec_run ? c->d_spec_run_ctl : (spectral ? c->d_spec_ctl : nullptr),
+                 spec_run ? sp2::kSpecRunCtl + c->spec_run_grid
+                          : (sp2::kMaxIter + 2) * sp2::kSpecCtl,
+                 s));
   if (c->bsr) {
     SP2_HIP(c, sp2::launch_bsr_reset(c->b.ctr, s));
     SP2_HIP(c, sp2::launch_bsr_f0(c->b.F, c->b.m[0], c->b.nnzb_in, c->d_inst,
@@ -1006,15 +1038,31 @@ sp2_status run_batch(sp2_ctx c) {
     if (spectral) {
       // e_{i-1} in the spectral norm, from X~_{i-1} (the squares' input)
       if (timing) SP2_HIP(c, hipEventRecord(c->ev_nm[2 * i], s));
-      sp2::SpecArgs sa;
-      sa.inst = c->d_inst;
-      sa.chunks = c->d_spec_chunks;
-      sa.nchunks = c->spec_nchunks;
-      sa.count = count;
-      sa.iter = i;
-      sa.vec_cap = c->spec_vec_cap;
-      sa.ctl = c->d_spec_ctl + sp2::kSpecCtl * i;
-      SP2_HIP(c, sp2::launch_spectral(sa, c->fp64_store, c->spec_grid, s));
+      if (spec_run) {
+        sp2::SpecRunArgs ra;
+        ra.inst = c->d_inst;
+        ra.ctl = c->d_spec_run_ctl;
+        ra.phase = ra.ctl + sp2::kSpecRunCtl;
+        ra.err = ra.ctl + sp2::kSpecRunErr;
+        ra.data = c->d_spec_run;
+        ra.dots = ra.data + 2 * sp2::kSpecRunMax;
+        ra.hist = ra.dots + 2 * sp2::kSpecRunMax;
+        ra.iter = i;
+        ra.wait_limit = c->wait_ms * c->wall_khz;
+        SP2_HIP(c, sp2::launch_spectral_resident(ra, c->fp64_store,
+                                                 static_cast<int>(c->hi[0].n), c->num_cus,
+                                                 c->spec_run_grid, s));
+      } else {
+        sp2::SpecArgs sa;
+        sa.inst = c->d_inst;
+        sa.chunks = c->d_spec_chunks;
+        sa.nchunks = c->spec_nchunks;
+        sa.count = count;
+        sa.iter = i;
+        sa.vec_cap = c->spec_vec_cap;
+        sa.ctl = c->d_spec_ctl + sp2::kSpecCtl * i;
+        SP2_HIP(c, sp2::launch_spectral(sa, c->fp64_store, c->spec_grid, s));
+      }
       if (timing) SP2_HIP(c, hipEventRecord(c->ev_nm[2 * i + 1], s));
     }
     SP2_HIP(c, sp2::launch_finalize(c->d_inst, count, c->d_part, c->d_part_f0,
@@ -1032,7 +1080,15 @@ sp2_status run_batch(sp2_ctx c) {
   SP2_HIP(c, hipMemcpyAsync(c->host_state.data(), c->d_st,
                             count * sizeof(DevState), hipMemcpyDeviceToHost,
                             s));
+  int32_t spec_err = 0;
+  if (spec_run)
+    SP2_HIP(c, hipMemcpyAsync(&spec_err, c->d_spec_run_ctl + sp2::kSpecRunErr,
+                              sizeof(spec_err), hipMemcpyDeviceToHost, s));
   SP2_HIP(c, hipStreamSynchronize(s));
+  if (spec_err != 0)
+    return fail(c, SP2_HIP_ERROR,
+                "spectral norm: a workgroup waited for the others longer than "
+                "its limit", hipSuccess);
   int32_t steps = 0;
   for (const DevState& h : c->host_state) {
     if (!h.done)
@@ -1329,6 +1385,8 @@ sp2_status sp2_destroy(sp2_ctx c) {
   rel(c->d_spec);
   rel(c->d_spec_chunks);
   rel(c->d_spec_ctl);
+  rel(c->d_spec_run_ctl);
+  rel(c->d_spec_run);
   rel(c->s_pool);
   rel(c->s_split[0]);
   rel(c->s_split[1]);

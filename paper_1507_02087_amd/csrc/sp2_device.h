@@ -406,6 +406,43 @@ constexpr int kSpecCtl = 1;
 // global memory.
 constexpr int kSpecLdsVec = 8192;
 
+// Entry `row` of the Lanczos start vector of the spectral norm: SplitMix64's
+// output for the row index, mapped to [-1, 1). A fixed pseudo-random vector
+// has a component along every eigenvector of E except by accident.
+__device__ __forceinline__ double spec_start_entry(int row) {
+  uint64_t z = static_cast<uint64_t>(row) * 0x9E3779B97F4A7C15ull +
+               0x9E3779B97F4A7C15ull;
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  z ^= z >> 31;
+  return static_cast<double>(z >> 11) * 0x1.0p-52 - 1.0;
+}
+
+// The spectral norm of one dense instance from an iterate held in registers
+// (spectral_run.hip). Phases are numbered 256 iter + 1, ... so that nothing
+// has to be cleared between the launches of a run; phase, ctl and err are
+// zero at its start.
+constexpr int kSpecRunMax = 4096;          // rows at most
+constexpr int kSpecRunCount = 0;           // ctl: 256 iter + coefficients posted
+constexpr int kSpecRunStop = 32;           // ctl: iter once its estimate is final
+constexpr int kSpecRunErr = 64;            // ctl: nonzero after a wait past its limit
+constexpr int kSpecRunCtl = 96;            // words of ctl, then a phase per workgroup
+struct SpecRunArgs {
+  const Instance* inst;
+  int32_t* ctl;
+  int32_t* phase;         // per workgroup
+  int32_t* err;
+  double* data;           // 2 x kSpecRunMax: a product's output, by parity
+  double* dots;           // 2 x kSpecRunMax: per wave q_j . w_j
+  double* hist;           // alpha_j, beta_j
+  int iter;
+  long long wait_limit;
+};
+// Workgroups of the launch, 0 when the iterate does not fit.
+int spectral_resident_grid(bool fp64_store, int n, int num_cus);
+hipError_t launch_spectral_resident(const SpecRunArgs& a, bool fp64_store, int n, int num_cus,
+                                    int grid, hipStream_t s);
+
 // Host-side launchers (implemented in the .hip files).
 // Clears the states and the batch's done counter; `zero` (may be null)
 // names `nzero` further counters to clear.

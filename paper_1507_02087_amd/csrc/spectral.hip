@@ -74,18 +74,6 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
   return t;
 }
 
-// Entry `row` of the start vector: SplitMix64's output for the row index,
-// mapped to [-1, 1). A fixed pseudo-random vector has a component along
-// every eigenvector of E except by accident.
-__device__ __forceinline__ double start_entry(int row) {
-  uint64_t z = static_cast<uint64_t>(row) * 0x9E3779B97F4A7C15ull +
-               0x9E3779B97F4A7C15ull;
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  z ^= z >> 31;
-  return static_cast<double>(z >> 11) * 0x1.0p-52 - 1.0;
-}
-
 // Native vector types (HIP's float4/double2 are classes whose copies go
 // through generic references, which would turn the loads below into flat
 // loads).
@@ -405,7 +393,7 @@ __global__ __launch_bounds__(kThreads, 2) void spectral_kernel(SpecArgs a) {
     const int lc = c - in.sp_ch0;
     if (threadIdx.x < kSpecRows) {
       const int row = ch.y + threadIdx.x;
-      v.w[row] = (row < in.n) ? start_entry(row) : 0.0;
+      v.w[row] = (row < in.n) ? spec_start_entry(row) : 0.0;
       v.q[row] = 0.0;
       v.q[ldq + row] = 0.0;
     }
