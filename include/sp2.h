@@ -120,8 +120,9 @@ typedef enum {
                                 library's cost model finds it the faster
                                 driver: one cooperative launch for the whole
                                 run (affine start, every step, the stop) in
-                                which each instance has a fixed team of
-                                workgroups, with square kernels of its own.
+                                which each instance has a team of workgroups
+                                (of its own, or one that works through a list
+                                of instances), with square kernels of its own.
                                 Otherwise persistent for a batch of more than
                                 one instance with the Frobenius norm (Alg. 2
                                 or SP2-ACC), else a launch sequence per

@@ -35,6 +35,10 @@ struct RunInst {
 struct RunPlan {
   int mb = 0;                    // tile edge / 16 (0: no plan fits)
   std::vector<RunSeat> seats;    // one per workgroup
+  int teams = 0;
+  // instances that the teams take one after another, largest first, when
+  // there are more than teams (empty: a team per instance)
+  std::vector<int32_t> pull;
   double step_us = 0.0;          // estimated time of one product
 };
 

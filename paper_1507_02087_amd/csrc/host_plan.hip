@@ -112,7 +112,7 @@ RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edg
   const int count = static_cast<int>(inst.size());
   RunPlan best;
   std::vector<int> best_size;
-  int best_cap = 0;
+  int best_cap = 0, best_team = 0;
   for (int q = 0; edges[q]; ++q) {
     // a single run in FP32 or BF16x3 takes one workgroup per CU: its four
     // waves alone keep the matrix cores busy, and a second workgroup only
@@ -123,7 +123,7 @@ RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edg
     const int mb = edges[q], bm = 16 * mb;
     const int cap =
         (count == 1 && precision != 0) ? std::min(grids[q], num_cus) : grids[q];
-    if (cap < count) continue;
+    if (cap < 1) continue;
     std::vector<int64_t> tiles(count);
     std::vector<double> tile_us(count);
     int64_t total = 0;
@@ -166,28 +166,67 @@ RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edg
       return s;
     };
     hi *= 1.0001;
-    if (seats_for(hi, nullptr) > cap) continue;
-    double work = 0.0;
-    for (int b = 0; b < count; ++b) work += tile_us[b] * static_cast<double>(tiles[b]);
+    // Teams of equal size that take instances from a list: each step of an
+    // instance costs its team the rounds and the meeting, and the list is
+    // done when the teams' shares are, but not before its longest entry.
+    // (512 FP32 instances of 64 to 1024 rows: teams of 4 or 8 at 48- or
+    // 64-tiles 41 to 42 ms, of 16 43 to 44, the queue 48.8; 200 BF16x3 ones
+    // of 60 to 800 rows: teams of 8 at 64-tiles 7.2 ms, of 4 9.7, queue 10.3.)
+    for (int size = 1; size <= std::min(cap, 32); size *= 2) {
+      const int teams = cap / size / 8 * 8;   // the same number on every XCD
+      if (teams == 0 || teams >= count) continue;
+      double sum = 0.0, longest = 0.0;
+      for (int b = 0; b < count; ++b) {
+        if (inst[b].trivial) continue;
+        const double us = tile_us[b] * static_cast<double>((tiles[b] + size - 1) / size) +
+                          kRunMeetUs;
+        sum += us;
+        longest = std::max(longest, us);
+      }
+      // (per step of the batch, as the other estimates)
+      const double us = std::max(sum / teams, longest);
+      if (best.mb == 0 || us < best.step_us) {
+        best.mb = mb;
+        best.step_us = us;
+        best_cap = cap;
+        best_team = size;
+      }
+    }
+    if (cap < count || seats_for(hi, nullptr) > cap) continue;
     for (int it = 0; it < 40; ++it) {
       const double mid = 0.5 * (lo + hi);
       (seats_for(mid, nullptr) <= cap ? hi : lo) = mid;
     }
-    // Teams are fixed, so a batch whose largest instances get too few seats
-    // leaves most of the device idle; the queue of the persistent driver
-    // deals its tiles out instead (512 FP32 instances of 64 to 1024 rows on
-    // 512 seats: 152 ms against 67). Its step costs the instances' share of
-    // the device and some 30 us of waiting and publishing.
-    if (hi + kRunMeetUs > 1.3 * work / cap + 30.0) continue;
     if (best.mb == 0 || hi + kRunMeetUs < best.step_us) {
       best.mb = mb;
       best_cap = cap;
       best.step_us = hi + kRunMeetUs;
+      best_team = 0;
       best_size.assign(count, 0);
       seats_for(hi, &best_size);
     }
   }
   if (best.mb == 0) return best;
+  if (best_team > 0) {
+    // the list, largest first; team t starts with its t-th entry. A team's
+    // seats are consecutive in an XCD's column of the grid.
+    std::vector<int32_t> list(count);
+    for (int b = 0; b < count; ++b) list[b] = b;
+    std::stable_sort(list.begin(), list.end(), [&](int32_t a, int32_t b) {
+      return (inst[a].trivial ? 0 : inst[a].n) > (inst[b].trivial ? 0 : inst[b].n);
+    });
+    const int X = 8, teams = best_cap / best_team / 8 * 8;
+    best.teams = teams;
+    const int rows = teams / X * best_team;
+    best.seats.assign(static_cast<size_t>(rows) * X, RunSeat{0, 0, 0, 0, 0, 0});
+    for (int t = 0; t < teams; ++t)
+      for (int r = 0; r < best_team; ++r)
+        best.seats[static_cast<size_t>(t / X * best_team + r) * X + t % X] =
+            RunSeat{list[t], r, best_team, t * best_team, 0, t};
+    best.pull.assign(list.begin() + teams, list.end());
+    return best;
+  }
+  best.teams = count;
   // Workgroup b runs on XCD b mod 8: a team of up to 32 workgroups (the CUs
   // of an XCD) goes to the least loaded XCD, whose L2 then serves all its
   // exchanges; a larger one is dealt in eight contiguous parts, so that
@@ -218,20 +257,20 @@ RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edg
     const int x = least();
     const bool fits = (count == 1) ? size * X <= best_cap : col[x].size() + size <= rows;
     if (size <= 32 && fits) {
-      for (int r = 0; r < size; ++r) col[x].push_back(RunSeat{b, r, size, base[b], 0});
+      for (int r = 0; r < size; ++r) col[x].push_back(RunSeat{b, r, size, base[b], 0, b});
     } else {
       int r = 0;
       for (int y = 0; y < X; ++y) {
         const int part = (size - r + X - y - 1) / (X - y);
         for (int k = 0; k < part && col[y].size() < rows; ++k)
-          col[y].push_back(RunSeat{b, r++, size, base[b], 0});
+          col[y].push_back(RunSeat{b, r++, size, base[b], 0, b});
       }
-      while (r < size) col[least()].push_back(RunSeat{b, r++, size, base[b], 0});
+      while (r < size) col[least()].push_back(RunSeat{b, r++, size, base[b], 0, b});
     }
   }
   size_t depth = 0;
   for (const auto& c : col) depth = std::max(depth, c.size());
-  best.seats.assign(depth * X, RunSeat{0, 0, 0, 0, 0});
+  best.seats.assign(depth * X, RunSeat{0, 0, 0, 0, 0, 0});
   for (int x = 0; x < X; ++x)
     for (size_t k = 0; k < col[x].size(); ++k) best.seats[k * X + x] = col[x][k];
   // The last round's tiles go to the seats of the lowest rows of the grid

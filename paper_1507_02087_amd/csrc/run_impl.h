@@ -61,8 +61,9 @@ struct RunType<2> {
   using AccV = floatx4;
 };
 
-// Precision P, tiles of 16 MB rows, NW waves.
-template <int P_, int MB_, int NW_>
+// Precision P, tiles of 16 MB rows, NW waves. SOLO: for single runs, one
+// workgroup per CU where that buys registers.
+template <int P_, int MB_, int NW_, bool SOLO>
 struct RunCfg {
   static constexpr int P = P_, MB = MB_, NW = NW_;
   using T = typename RunType<P>::T;
@@ -87,15 +88,15 @@ struct RunCfg {
   static constexpr int SMEM = R * SLOT * static_cast<int>(sizeof(T));
   // waves per SIMD the registers are budgeted for: one where the two sets of
   // accumulators need more than half of them
-  static constexpr int WAVES = (P == 1 && MB >= 4) ? 1 : 2;
-  static_assert(SMEM <= (MB <= 3 ? 78 : 156) * 1024, "LDS of a CU");
+  static constexpr int WAVES = (SOLO && P == 1 && MB >= 4) ? 1 : 2;
+  static_assert(SMEM <= (MB <= 4 ? 78 : 156) * 1024, "LDS of a CU");
   // every operand block lies within the padded matrix
   static_assert(BM % KO == 0, "whole operand blocks per tile");
   // operand sets in flight
-  static constexpr int DEPTH = (P == 2) ? (MB >= 3 ? 2 : 4) : (MB == 2 ? 6 : (P == 0 && MB == 4 ? 2 : 3));
+  static constexpr int DEPTH = (P == 2) ? (MB >= 3 ? 2 : 4) : (MB == 2 ? 6 : (MB == 4 && WAVES == 2 ? 2 : 3));
   // the old values are loaded before the main loop and the next tile's first
   // sets before the epilogue, where the registers hold them
-  static constexpr bool AHEAD = (P == 1) || MB <= 2;
+  static constexpr bool AHEAD = (P == 1 && (MB <= 3 || WAVES == 1)) || MB <= 2;
   // FP64 (where the registers allow) and FP32: after CHAIN blocks of columns
   // the running sums go into a second set of accumulators, so that rounding
   // grows with the chain and not with the wave's whole K part
@@ -502,9 +503,15 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES) void run_kernel(RunArgs a) {
   __shared__ double sh[C::NW][3];
   __shared__ int word;
   const auto* seat = cro(a.seats + blockIdx.x);
-  const int inst = seat->inst, rank = seat->rank, size = seat->size, base = seat->base;
-  const int last_tile = seat->last;
+  const int rank = seat->rank, size = seat->size, base = seat->base, team = seat->team;
   if (size == 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = run_uni(tid >> 6);
+  const bool affine = a.stretch != 0;
+  double* const ec = a.coef + 8 * team;   // StepCoef of the next product
+  int32_t* const flag = a.flag + 32 * team;
+  int phase = 0;
+  int inst = seat->inst;
+  for (;;) {
   const Instance& gin = a.inst[inst];
   const auto* in = cro(a.inst + inst);
   DevState* const st = in->st;
@@ -517,16 +524,13 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES) void run_kernel(RunArgs a) {
   T* const Sq = static_cast<T*>(in->S);
   __bf16* const SH = static_cast<__bf16*>(in->SH);
   __bf16* const SL = static_cast<__bf16*>(in->SL);
-  const bool affine = a.stretch != 0;
-  double* const ec = a.coef + 8 * inst;   // StepCoef of the next product
-  const int tid = threadIdx.x, lane = tid & 63, wave = run_uni(tid >> 6);
   const int kb = (n + C::KO - 1) / C::KO;
   const int chain = (C::P == 0 && n > a.chain_n) ? kb : C::CHAIN;
   const int np = (n + C::BM - 1) / C::BM * C::BM;
-  int phase = 0;
   // tiles of this workgroup: rank, rank + size, ... over the whole rounds,
   // then its tile of the incomplete last round, if it has one
   const int whole = ntiles / size * size;
+  const int last_tile = a.npull ? whole + rank : seat->last;
   auto first_tile = [&]() { return whole > 0 ? rank : last_tile; };
   auto next_tile = [&](int t) {
     return t + size < whole ? t + size : (t < whole ? last_tile : ntiles);
@@ -565,7 +569,7 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES) void run_kernel(RunArgs a) {
       if (tid == 0) {
         __hip_atomic_store(&post[rank].phase, phase, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-        word = run_wait(a.flag + 32 * inst, 4 * phase, a.err, a.wait_limit);
+        word = run_wait(flag, 4 * phase, a.err, a.wait_limit);
       }
     } else {
       double pv = 0.0, p1 = 0.0, p2 = 0.0;
@@ -610,7 +614,7 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES) void run_kernel(RunArgs a) {
             }
           }
           if (size > 1)
-            __hip_atomic_store(a.flag + 32 * inst, word, __ATOMIC_RELAXED,
+            __hip_atomic_store(flag, word, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
       }
@@ -678,6 +682,34 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES) void run_kernel(RunArgs a) {
               Hb[nxt], Lb[nxt], k2, tau);
     }
     w = meet(true, iter, sums);
+  }
+  if (w < 0 || a.npull == 0) return;
+  // A team of a batch takes the next instance of the list. Its number has a
+  // word of its own: nobody has posted since the release word, which a slower
+  // member may still be about to read.
+  ++phase;
+  if (tid == 0) {
+    int next = 0;
+    if (rank == 0) {
+      const int k = __hip_atomic_fetch_add(a.next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      next = (k < a.npull) ? a.pull[k] : -1;
+      if (size > 1) {
+        __hip_atomic_store(flag + 1, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0);
+        __hip_atomic_store(flag + 2, phase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    } else {
+      next = (run_wait(flag + 2, phase, a.err, a.wait_limit) < 0) ? -1 : 0;
+      asm volatile("" ::: "memory");
+      if (next == 0)
+        next = __hip_atomic_load(flag + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    word = next;
+  }
+  __syncthreads();
+  inst = run_uni(word);
+  __syncthreads();
+  if (inst < 0) return;
   }
 }
 

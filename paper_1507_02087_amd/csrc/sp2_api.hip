@@ -201,7 +201,10 @@ struct sp2_ctx_s {
   const int2* d_run_tiles = nullptr;
   const Instance* d_run_inst = nullptr;
   std::vector<int> run_grids[3][2];   // co-resident workgroups per edge, by
-                                      // precision and McWeeny; found once
+                                      // precision and batch; found once
+  bool run_solo = true;
+  int run_teams = 0, run_npull = 0;
+  const int32_t* d_run_pull = nullptr;
   DevState* h_state = nullptr;     // pinned
   size_t h_state_cap = 0;
 
@@ -366,19 +369,22 @@ void release_groups(sp2_ctx c) {
 }
 
 // Co-resident workgroups of the resident run for every tile edge of the
-// context's precision.
-const std::vector<int>& run_grids(sp2_ctx c, bool mw) {
-  std::vector<int>& g = c->run_grids[c->opt.precision][mw ? 1 : 0];
+// context's precision (with and without McWeeny, which uses the same plan).
+const std::vector<int>& run_grids(sp2_ctx c, bool solo) {
+  std::vector<int>& g = c->run_grids[c->opt.precision][solo ? 1 : 0];
   if (g.empty())
     for (const int* e = sp2::run_edges(c->opt.precision); *e; ++e)
-      g.push_back(sp2::run_max_grid(c->opt.precision, *e, mw, c->num_cus));
+      g.push_back(std::min(
+          sp2::run_max_grid(c->opt.precision, *e, false, solo, c->num_cus),
+          sp2::run_max_grid(c->opt.precision, *e, true, solo, c->num_cus)));
   return g;
 }
 
 // Words of a resident run's exchange, cleared before it: the error word and
-// a line per instance's release word, then the seats' posts.
-size_t run_sync_words(int count, size_t seats) {
-  return 32 * (static_cast<size_t>(count) + 1) +
+// the next instance of the list, a line per team's release word, then the
+// seats' posts.
+size_t run_sync_words(int teams, size_t seats) {
+  return 32 * (static_cast<size_t>(teams) + 1) +
          seats * (sizeof(sp2::RunPost) / sizeof(int32_t));
 }
 
@@ -404,11 +410,9 @@ bool choose_resident(sp2_ctx c, sp2::RunPlan* plan) {
   for (const HostInst& h : c->hi)
     if (h.n > most) return false;
   for (const HostInst& h : c->hi) inst.push_back(sp2::RunInst{h.n, h.n_occ == 0 || h.n_occ == h.n});
-  // a McWeeny run uses the same plan, so both kernels have to fit
-  std::vector<int> g = run_grids(c, false);
-  const std::vector<int>& gm = run_grids(c, true);
-  for (size_t q = 0; q < g.size(); ++q) g[q] = std::min(g[q], gm[q]);
-  *plan = sp2::plan_run(inst, o.precision, sp2::run_edges(o.precision), g, c->num_cus);
+  const bool solo = inst.size() == 1;
+  *plan = sp2::plan_run(inst, o.precision, sp2::run_edges(o.precision),
+                        run_grids(c, solo), c->num_cus);
   return plan->mb != 0;
 }
 
@@ -438,8 +442,8 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   // release words, the posts of the seats and the coefficients
   SP2_HIP(c, grow(c, c->d_st, c->d_st_cap,
                   count * sizeof(DevState) +
-                      run_sync_words(count, plan.seats.size()) * sizeof(int32_t) +
-                      count * 8 * sizeof(double), s));
+                      run_sync_words(plan.teams, plan.seats.size()) * sizeof(int32_t) +
+                      plan.teams * 8 * sizeof(double), s));
   std::vector<int2> tiles;
   std::vector<Instance> inst(count);
   for (int b = 0; b < count; ++b) {
@@ -471,10 +475,13 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   }
   const size_t ib = (count * sizeof(Instance) + 255) / 256 * 256;
   const size_t sb = (plan.seats.size() * sizeof(sp2::RunSeat) + 255) / 256 * 256;
-  std::vector<char> blob(ib + sb + tiles.size() * sizeof(int2));
+  const size_t tb = (tiles.size() * sizeof(int2) + 255) / 256 * 256;
+  std::vector<char> blob(ib + sb + tb + plan.pull.size() * sizeof(int32_t));
   memcpy(blob.data(), inst.data(), count * sizeof(Instance));
   memcpy(blob.data() + ib, plan.seats.data(), plan.seats.size() * sizeof(sp2::RunSeat));
   memcpy(blob.data() + ib + sb, tiles.data(), tiles.size() * sizeof(int2));
+  if (!plan.pull.empty())
+    memcpy(blob.data() + ib + sb + tb, plan.pull.data(), plan.pull.size() * sizeof(int32_t));
   SP2_HIP(c, grow(c, c->d_run, c->d_run_cap, blob.size(), s));
   SP2_HIP(c, hipMemcpyAsync(c->d_run, blob.data(), blob.size(), hipMemcpyHostToDevice, s));
   SP2_HIP(c, hipStreamSynchronize(s));
@@ -482,6 +489,10 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   c->d_run_inst = reinterpret_cast<const Instance*>(base);
   c->d_seats = reinterpret_cast<const sp2::RunSeat*>(base + ib);
   c->d_run_tiles = reinterpret_cast<const int2*>(base + ib + sb);
+  c->d_run_pull = reinterpret_cast<const int32_t*>(base + ib + sb + tb);
+  c->run_npull = static_cast<int>(plan.pull.size());
+  c->run_teams = plan.teams;
+  c->run_solo = (count == 1);
   c->run_mb = plan.mb;
   c->run_grid = static_cast<int>(plan.seats.size());
   const size_t hb = count * sizeof(DevState) + 256;
@@ -887,9 +898,12 @@ sp2_status run_resident(sp2_ctx c) {
   a.seats = c->d_seats;
   a.tiles = c->d_run_tiles;
   a.err = err;
+  a.next = err + 1;
+  a.pull = c->d_run_pull;
+  a.npull = c->run_npull;
   a.flag = err + 32;
-  a.post = reinterpret_cast<sp2::RunPost*>(a.flag + 32 * count);
-  const size_t words = run_sync_words(count, c->run_grid);
+  a.post = reinterpret_cast<sp2::RunPost*>(a.flag + 32 * c->run_teams);
+  const size_t words = run_sync_words(c->run_teams, c->run_grid);
   a.coef = reinterpret_cast<double*>(err + words);
   a.ndone = c->d_ndone;
   a.count = count;
@@ -902,7 +916,8 @@ sp2_status run_resident(sp2_ctx c) {
   SP2_HIP(c, hipEventRecord(c->ev_start, s));
   SP2_HIP(c, sp2::launch_state_reset(c->d_st, count, c->d_ndone, err,
                                      static_cast<int>(words), s));
-  SP2_HIP(c, sp2::launch_run(c->opt.precision, c->run_mb, c->mcweeny, a, c->run_grid, s));
+  SP2_HIP(c, sp2::launch_run(c->opt.precision, c->run_mb, c->mcweeny, c->run_solo, a,
+                             c->run_grid, s));
   SP2_HIP(c, hipEventRecord(c->ev_stop, s));
   SP2_HIP(c, hipMemcpyAsync(c->h_state, c->d_st,
                             count * sizeof(DevState) + sizeof(int32_t),

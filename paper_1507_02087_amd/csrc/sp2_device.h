@@ -347,13 +347,13 @@ __host__ __device__ __forceinline__ size_t op_off(int row, int col, int ld) {
 }
 
 // Resident runs: one cooperative launch for a whole run. Each workgroup has
-// a seat: its instance, its rank in the instance's team, the team's size
+// a seat: its (first) instance, its rank in its team, the team's size
 // (0: the seat is empty), the team's first slot in the partial sums, and the
 // seat's tile in the last round when size does not divide the tiles (a tile
 // index past the last: none). The seats that have one are spread evenly over
 // the CUs.
 struct RunSeat {
-  int32_t inst, rank, size, base, last;
+  int32_t inst, rank, size, base, last, team;
 };
 // What a seat posts once per product: its partial sums and the phase.
 struct RunPost {
@@ -365,9 +365,13 @@ struct RunArgs {
   const RunSeat* seats;
   const int2* tiles;
   RunPost* post;          // per seat, phase 0 at launch
-  int32_t* flag;          // per instance 32 words, [0] zero at launch: the
-                          // word that releases the team
-  double* coef;           // per instance 8: StepCoef of the next product
+  int32_t* flag;          // per team 32 words, zero at launch: [0] the word
+                          // that releases the team, [1] its next instance,
+                          // [2] the phase that [1] belongs to
+  double* coef;           // per team 8: StepCoef of the next product
+  const int32_t* pull;    // instances that the teams take one after another
+  int32_t* next;          // zero at launch: the next one of them
+  int32_t npull;          // their number (0: a team per instance)
   int32_t* ndone;
   int32_t* err;           // nonzero once a wait exceeded its limit
   int32_t count;          // instances
@@ -379,8 +383,9 @@ struct RunArgs {
 // compiled for, smallest first, ended by 0.
 const int* run_edges(int precision);
 // Workgroups of the resident run that fit on the device at once (0: none).
-int run_max_grid(int precision, int mb, bool mw, int num_cus);
-hipError_t launch_run(int precision, int mb, bool mw, const RunArgs& a, int grid,
+// `solo`: the kernel of single runs, else that of batches.
+int run_max_grid(int precision, int mb, bool mw, bool solo, int num_cus);
+hipError_t launch_run(int precision, int mb, bool mw, bool solo, const RunArgs& a, int grid,
                       hipStream_t s);
 // D = (X - c I) / a from an iterate in operand order; `symmetric` reads the
 // upper triangle only.

@@ -15,7 +15,7 @@ int main() {
   int bad = 0, planned = 0;
   for (int it = 0; it < 2000; ++it) {
     const int prec = g() % 3;
-    const int count = it < 700 ? 1 : 1 + g() % (it % 2 ? 20 : 400);
+    const int count = it < 700 ? 1 : 1 + g() % (it % 2 ? 20 : 900);
     const int cus = (it % 7 == 0) ? 32 : 256;
     std::vector<sp2::RunInst> in(count);
     for (auto& i : in) {
@@ -34,6 +34,33 @@ int main() {
     for (int q = 0; edges[prec][q]; ++q)
       if (edges[prec][q] == p.mb) cap = grids[q];
     if (static_cast<int>(p.seats.size()) > cap) fail("grid over the device");
+    if (!p.pull.empty()) {
+      // equal teams: every rank of every team once, first entries and list
+      // together every instance once
+      std::vector<int> seen(count, 0), slot(p.seats.size(), 0);
+      std::vector<int> members(p.teams, 0), first(p.teams, -1);
+      for (const sp2::RunSeat& s : p.seats) {
+        if (s.size == 0) continue;
+        if (s.team < 0 || s.team >= p.teams || s.rank < 0 || s.rank >= s.size ||
+            s.base + s.rank >= static_cast<int>(p.seats.size()) || s.inst < 0 ||
+            s.inst >= count || (first[s.team] >= 0 && first[s.team] != s.inst)) {
+          fail("list seat");
+          continue;
+        }
+        first[s.team] = s.inst;
+        members[s.team] += 1 << s.rank % 30;
+        slot[s.base + s.rank]++;
+        if (s.rank == 0) seen[s.inst]++;
+      }
+      for (int c : slot)
+        if (c > 1) fail("list slot");
+      for (int t = 0; t < p.teams; ++t)
+        if (first[t] < 0 || members[t] == 0) fail("empty team");
+      for (int32_t b : p.pull) seen[b]++;
+      for (int c : seen)
+        if (c != 1) fail("list");
+      continue;
+    }
     std::vector<std::vector<int>> ranks(count), hit(count);
     std::vector<int> size(count, 0), ntile(count), slot(p.seats.size(), 0);
     for (int b = 0; b < count; ++b) {

@@ -131,7 +131,9 @@ def test_batch_teams(prec):
     import torch
     import paper_1507_02087_amd as sp2
     rng = np.random.default_rng(3)
-    for sizes in ([600, 33, 64], [int(x) for x in rng.integers(8, 140, 60)]):
+    # (600 instances: teams that take one after another from a list)
+    for sizes in ([600, 33, 64], [int(x) for x in rng.integers(8, 140, 60)],
+                  [int(x) for x in rng.integers(8, 160, 600)]):
         insts = [dense_instance(n, max(1, n // 3), -1.0, 1.0, 0.1, seed=40 + k)
                  for k, n in enumerate(sizes)]
         Fs = [torch.from_numpy(i.F).cuda() for i in insts] + [torch.eye(5, dtype=torch.float64).cuda()]
@@ -140,8 +142,10 @@ def test_batch_teams(prec):
         print_case(f"resident batch {prec} of {len(Fs)}")
         a, _ = sp2.run_batch(Fs, lo, hi, no, precision=prec)
         b, _ = sp2.run_batch(Fs, lo, hi, no, precision=prec)
-        for inst, r, s in zip(insts, a, b):
+        for k, (inst, r, s) in enumerate(zip(insts, a, b)):
             assert r.status == sp2.OK and r.n == s.n and torch.equal(r.D, s.D)
+            if k % max(1, len(insts) // 60):
+                continue
             De = oracle.density_from_eigenvectors(inst.Q, inst.n_occ)
             err = float(np.linalg.norm(r.D.cpu().numpy() - De)) / math.sqrt(inst.n_occ)
             assert err < D_TOL[prec], (inst.n, err)
