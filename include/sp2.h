@@ -361,6 +361,17 @@ sp2_status sp2_batch_get(sp2_ctx ctx, int32_t idx, void* D_dev, int64_t ldd,
                          int32_t as_fp64, int32_t* n_iter, int32_t* n_squares,
                          int32_t* status);
 
+/* sp2_batch_get for every instance of the last run at once: D_dev[b] (row
+ * stride ldd[b] >= n of instance b) receives instance b's density, and
+ * n_iter[b], n_squares[b], status[b] its outcome; D_dev (with ldd) and each of
+ * the outcome arrays may be NULL. The copies are complete on return. `count`
+ * must be the number of instances. Errors: SP2_BAD_STATE before a completed
+ * run, SP2_INVALID_ARG. */
+sp2_status sp2_batch_get_all(sp2_ctx ctx, int32_t count, void* const* D_dev,
+                             const int64_t* ldd, int32_t as_fp64,
+                             int32_t* n_iter, int32_t* n_squares,
+                             int32_t* status);
+
 /* History of instance idx, with the conventions of sp2_get_history. */
 sp2_status sp2_batch_get_history(sp2_ctx ctx, int32_t idx, int32_t cap,
                                  int32_t* len, double* v, double* t1,

@@ -67,6 +67,8 @@ SIGNATURES = {
     "sp2_batch_get": (_c.c_int, [_c.c_void_p, _c.c_int32, _c.c_void_p, _c.c_int64,
                                  _c.c_int32, _c.POINTER(_c.c_int32),
                                  _c.POINTER(_c.c_int32), _c.POINTER(_c.c_int32)]),
+    "sp2_batch_get_all": (_c.c_int, [_c.c_void_p, _c.c_int32, _c.c_void_p, _c.c_void_p,
+                                     _c.c_int32, _c.c_void_p, _c.c_void_p, _c.c_void_p]),
     "sp2_batch_get_history": (_c.c_int, [_c.c_void_p, _c.c_int32, _c.c_int32,
                                          _c.POINTER(_c.c_int32), _c.c_void_p,
                                          _c.c_void_p, _c.c_void_p, _c.c_void_p,
@@ -504,18 +506,39 @@ class BatchContext(Context):
             ctypes.byref(stt)), "sp2_batch_get")
         return out, stt.value, it.value, sq.value
 
-    def batch_history(self, idx: int, cap: int = MAX_ITER_LIMIT + 2):
+    def batch_get_all(self, as_fp64: bool = True):
+        """batch_get of every instance at once: (densities, status, n,
+        n_squares), each a list with one entry per instance."""
+        import torch
+        dt = torch.float64 if (as_fp64 or self._prec == "fp64") else torch.float32
+        dev = f"cuda:{self.device}"
+        Ds = [torch.empty((n, n), dtype=dt, device=dev) for n in self._ns]
+        m = len(Ds)
+        ptrs = _arr(ctypes.c_void_p, [D.data_ptr() for D in Ds])
+        lds = _arr(ctypes.c_int64, self._ns)
+        it, sq, st = ((ctypes.c_int32 * m)() for _ in range(3))
+        self._check(self._lib.sp2_batch_get_all(self._h, m, ptrs, lds, 1 if as_fp64 else 0,
+                                                it, sq, st), "sp2_batch_get_all")
+        return Ds, list(st), list(it), list(sq)
+
+    def _history_reader(self, cap: int = MAX_ITER_LIMIT + 2):
+        """idx -> batch_history(idx), reading into one set of arrays."""
         import numpy as np
         ln = ctypes.c_int32()
         v, t1, t2, r = (np.full(cap, np.nan) for _ in range(4))
         p = np.full(cap, -1, dtype=np.int8)
-        ptr = lambda a: ctypes.c_void_p(a.ctypes.data)  # noqa: E731
-        self._check(self._lib.sp2_batch_get_history(
-            self._h, idx, cap, ctypes.byref(ln), ptr(v), ptr(t1), ptr(t2), ptr(p),
-            ptr(r)), "sp2_batch_get_history")
-        m = ln.value
-        return dict(v=v[:m].tolist(), r=r[:m].tolist(), t1=t1[:m + 1].tolist(),
-                    t2=t2[:m + 1].tolist(), p=p[:m + 1].astype(int).tolist())
+        args = [ctypes.byref(ln)] + [ctypes.c_void_p(a.ctypes.data) for a in (v, t1, t2, p, r)]
+
+        def read(idx: int):
+            self._check(self._lib.sp2_batch_get_history(self._h, idx, cap, *args),
+                        "sp2_batch_get_history")
+            m = ln.value
+            return dict(v=v[:m].tolist(), r=r[:m].tolist(), t1=t1[:m + 1].tolist(),
+                        t2=t2[:m + 1].tolist(), p=p[:m + 1].tolist())
+        return read
+
+    def batch_history(self, idx: int, cap: int = MAX_ITER_LIMIT + 2):
+        return self._history_reader(cap)(idx)
 
     def batch_run_time(self):
         ms, steps = ctypes.c_double(), ctypes.c_int32()
@@ -543,11 +566,12 @@ def run_batch(Fs, lambda_min, lambda_max, n_occ, ctx: BatchContext | None = None
         ctx.batch_run()
         ms, _ = ctx.batch_run_time()
         out = []
+        Ds, sts, ns, sqs = ctx.batch_get_all(as_fp64=as_fp64)
+        hist = ctx._history_reader()
         for b in range(len(Fs)):
-            D, st, n, sq = ctx.batch_get(b, as_fp64=as_fp64)
             m = ctx.get_norm_history(b) if opts.get("norm", "fro") != "fro" else []
-            out.append(Result(D=D, status=st, n=n, n_squares=sq, run_ms=ms, m=m,
-                              **ctx.batch_history(b)))
+            out.append(Result(D=Ds[b], status=sts[b], n=ns[b], n_squares=sqs[b], run_ms=ms,
+                              m=m, **hist(b)))
         return out, ms
     finally:
         if own:

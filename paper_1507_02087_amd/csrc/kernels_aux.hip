@@ -320,17 +320,16 @@ __global__ __launch_bounds__(kThreads) void copy_out_sym_kernel(
 
 // The same from an iterate in operand order: block (bi, bj) of 32 x 32 is
 // read as whole operand blocks (contiguous kilobytes) into LDS and written
-// as rows. With kSym only blocks bi <= bj are read, and each is also written
+// as rows. With `sym` only blocks bi <= bj are read, and each is also written
 // transposed.
-template <typename Tin, typename Tout, bool kSym>
-__global__ __launch_bounds__(kThreads) void copy_out_op_kernel(
-    const Tin* __restrict__ X, int n, int ldx, OpMap m, Tout* __restrict__ D,
-    int64_t ldd) {
+template <typename Tin, typename Tout>
+__device__ __forceinline__ void copy_op_block(const Tin* __restrict__ X, int n, int ldx,
+                                              OpMap m, Tout* __restrict__ D, int64_t ldd,
+                                              bool sym, int bi, int bj) {
   constexpr int B = 32, V = 16 / sizeof(Tin), KC = 64 / sizeof(Tin), NC = B / KC;
   typedef Tin vec __attribute__((ext_vector_type(V)));
   __shared__ Tin t[B][B + 1];
-  const int bi = blockIdx.y, bj = blockIdx.x;
-  if (kSym && bi > bj) return;
+  if (sym && bi > bj) return;
   const int i0 = bi * B, j0 = bj * B;
   for (int v = threadIdx.x; v < B * B / V; v += kThreads) {
     const int blk = v / 64, l = v % 64;
@@ -350,17 +349,42 @@ __global__ __launch_bounds__(kThreads) void copy_out_op_kernel(
     const int r = e / B, c = e % B;
     const int i = i0 + r, j = j0 + c;
     if (i < n && j < n) {
-      const Tin x = (kSym && bi == bj && r > c) ? t[c][r] : t[r][c];
+      const Tin x = (sym && bi == bj && r > c) ? t[c][r] : t[r][c];
       D[static_cast<int64_t>(i) * ldd + j] = val(x, i == j);
     }
   }
-  if (!kSym || bi == bj) return;
+  if (!sym || bi == bj) return;
   for (int e = threadIdx.x; e < B * B; e += kThreads) {
     const int r = e / B, c = e % B;
     const int i = j0 + r, j = i0 + c;
     if (i < n && j < n)
       D[static_cast<int64_t>(i) * ldd + j] = val(t[c][r], false);
   }
+}
+
+template <typename Tin, typename Tout, bool kSym>
+__global__ __launch_bounds__(kThreads) void copy_out_op_kernel(
+    const Tin* __restrict__ X, int n, int ldx, OpMap m, Tout* __restrict__ D,
+    int64_t ldd) {
+  copy_op_block<Tin, Tout>(X, n, ldx, m, D, ldd, kSym, blockIdx.y, blockIdx.x);
+}
+
+// Every density of a batch in one launch: jobs[j] owns the blocks first ..
+// of its 32-block grid.
+template <typename Tin, typename Tout>
+__global__ __launch_bounds__(kThreads) void copy_out_jobs_kernel(
+    const CopyJob* __restrict__ jobs, int count) {
+  const int b = blockIdx.x;
+  int lo = 0, hi = count;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) / 2;
+    if (jobs[mid].first <= b) lo = mid;
+    else hi = mid;
+  }
+  const CopyJob& j = jobs[lo];
+  const int nb = (j.n + 31) / 32, q = b - j.first;
+  copy_op_block<Tin, Tout>(static_cast<const Tin*>(j.X), j.n, j.ldx, j.m,
+                           static_cast<Tout*>(j.D), j.ldd, j.symmetric != 0, q / nb, q % nb);
 }
 
 int grid_for(int64_t total) {
@@ -420,6 +444,21 @@ hipError_t launch_copy_out_op(const void* X, bool fp64_store, int n, int ldx, vo
   if (fp64_store) return copy_out_op<double, double>(X, n, ldx, D, ldd, symmetric, m, s);
   if (out_fp64) return copy_out_op<float, double>(X, n, ldx, D, ldd, symmetric, m, s);
   return copy_out_op<float, float>(X, n, ldx, D, ldd, symmetric, m, s);
+}
+
+hipError_t launch_copy_out_jobs(const CopyJob* jobs, int count, int blocks, bool fp64_store,
+                                bool out_fp64, hipStream_t s) {
+  if (blocks == 0) return hipSuccess;
+  if (fp64_store)
+    hipLaunchKernelGGL((copy_out_jobs_kernel<double, double>), dim3(blocks), dim3(kThreads), 0,
+                       s, jobs, count);
+  else if (out_fp64)
+    hipLaunchKernelGGL((copy_out_jobs_kernel<float, double>), dim3(blocks), dim3(kThreads), 0,
+                       s, jobs, count);
+  else
+    hipLaunchKernelGGL((copy_out_jobs_kernel<float, float>), dim3(blocks), dim3(kThreads), 0, s,
+                       jobs, count);
+  return hipGetLastError();
 }
 
 hipError_t launch_copy_out(const void* X, bool fp64_store, int n, int ldx,

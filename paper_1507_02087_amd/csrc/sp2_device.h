@@ -393,6 +393,18 @@ hipError_t launch_copy_out_op(const void* X, bool fp64_store, int n, int ldx,
                               void* D, int64_t ldd, bool out_fp64, bool symmetric,
                               OpMap m, hipStream_t s);
 
+// The densities of a batch in one launch (iterates in operand order).
+struct CopyJob {
+  const void* X;
+  void* D;
+  int64_t ldd;
+  OpMap m;
+  int32_t n, ldx, symmetric;
+  int32_t first;   // first workgroup of the job
+};
+hipError_t launch_copy_out_jobs(const CopyJob* jobs, int count, int blocks, bool fp64_store,
+                                bool out_fp64, hipStream_t s);
+
 // Arguments of one spectral-norm launch: every running instance with a
 // chunk table entry (instance, first row) per kSpecRows rows.
 struct SpecArgs {

@@ -171,3 +171,37 @@ def test_wait_limit_reports_error(monkeypatch):
     finally:
         ctx.close()
     assert sp2.run_dense(F, -1.0, 1.0, 300).status == sp2.OK
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("kw", [{}, {"launch": "sequence"}, {"homo_lumo": True}])
+def test_all_densities_at_once(prec, kw):
+    """sp2_batch_get_all equals sp2_batch_get of every instance: resident and
+    row-major iterates, trivial and stretched instances, both output types."""
+    import torch
+    import paper_1507_02087_amd as sp2
+    insts = [dense_instance(n, n // 2, -1.0, 1.0, 0.1, seed=70 + n) for n in (2, 31, 64, 97, 200)]
+    Fs = [torch.from_numpy(i.F).cuda() for i in insts] + [torch.eye(9, dtype=torch.float64).cuda()]
+    no = [i.n_occ for i in insts] + [9]
+    m = len(Fs)
+    ctx = sp2.BatchContext(0)
+    try:
+        kw = dict(kw)
+        acc = kw.pop("homo_lumo", False)
+        ctx.batch_init(Fs, [-1.0] * m, [1.0] * m, no, precision=prec, **kw)
+        if acc:
+            b = [(float(i.lam[i.n_occ - 1]),) * 2 + (float(i.lam[i.n_occ]),) * 2 for i in insts]
+            b.append((-0.5, -0.5, 0.5, 0.5))
+            ctx.set_homo_lumo(*[list(c) for c in zip(*b)])
+        with pytest.raises(sp2.SP2Error) as e:
+            ctx.batch_get_all()
+        assert e.value.status == sp2.BAD_STATE
+        ctx.batch_run()
+        for as64 in (True, False):
+            Ds, st, it, sq = ctx.batch_get_all(as_fp64=as64)
+            for i in range(m):
+                D, s, n, q = ctx.batch_get(i, as_fp64=as64)
+                assert (st[i], it[i], sq[i]) == (s, n, q)
+                assert Ds[i].dtype == D.dtype and torch.equal(Ds[i], D), i
+    finally:
+        ctx.close()
