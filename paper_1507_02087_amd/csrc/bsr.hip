@@ -21,6 +21,7 @@
 // Blocks that truncation empties stay in Q with flag 0 and are skipped by
 // the next step, so values are never compacted. The index kernel (nonzero
 // blocks per row, in column order) serves the extraction of the result.
+#include "finalize_logic.h"
 #include "sp2_device.h"
 
 namespace sp2 {
@@ -65,9 +66,17 @@ __global__ __launch_bounds__(kScanThreads) void bsr_index_kernel(
     BsrMat M, int nb, BsrIndex idx) {
   __shared__ int32_t cnt[2 * kScanThreads];
   __shared__ int32_t sh[kScanThreads];
+  // eight flags of a row in flight at once
   for (int r = threadIdx.x; r < nb; r += kScanThreads) {
     int c = 0;
-    for (int q = M.row_ptr[r]; q < M.row_ptr[r + 1]; ++q) c += M.flag[q] ? 1 : 0;
+    const int q1 = M.row_ptr[r + 1];
+    for (int q = M.row_ptr[r]; q < q1; q += 8) {
+      int f[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] = (q + e < q1) ? M.flag[q + e] : 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) c += f[e] ? 1 : 0;
+    }
     cnt[r] = c;
   }
   __syncthreads();
@@ -76,12 +85,22 @@ __global__ __launch_bounds__(kScanThreads) void bsr_index_kernel(
 
   for (int r = threadIdx.x; r < nb; r += kScanThreads) {
     int o = idx.ptr[r];
-    for (int q = M.row_ptr[r]; q < M.row_ptr[r + 1]; ++q)
-      if (M.flag[q]) {
-        idx.col[o] = M.col[q];
-        idx.pos[o] = q;
-        ++o;
+    const int q1 = M.row_ptr[r + 1];
+    for (int q = M.row_ptr[r]; q < q1; q += 8) {
+      int f[8], col[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        f[e] = (q + e < q1) ? M.flag[q + e] : 0;
+        col[e] = (q + e < q1) ? M.col[q + e] : 0;
       }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (f[e]) {
+          idx.col[o] = col[e];
+          idx.pos[o] = q + e;
+          ++o;
+        }
+    }
   }
 }
 
@@ -93,12 +112,49 @@ __global__ __launch_bounds__(kScanThreads) void bsr_index_kernel(
 // into the LDS bitmap. Also counts the flagged blocks (statistics).
 constexpr int kCountThreads = 256;
 
+// With fin.part set, one workgroup more than rows takes the scalar step of
+// the product before (the finalize kernel's sums and finalize_scalar): the
+// pattern does not depend on it, and as a launch of its own it stood 5.3 us
+// of a 68 us step between two products. Its outcome is read by the kernels
+// after this one; a workgroup here that reads `done` as it is being set
+// counts a row that nobody uses, or does not.
 __global__ __launch_bounds__(kCountThreads) void bsr_symbolic_count_kernel(
     BsrMat A, int nb, int nbw, BsrSymbolic sym, BsrCounters* ctr,
-    const DevState* st, int iter) {
+    const DevState* st, int iter, BsrScalar fin) {
   __shared__ uint32_t bm[kMaxBlockCols / 32];
   __shared__ int32_t rk0[kCountThreads], pfx[kCountThreads + 1];
   __shared__ int32_t wsum[kCountThreads / 64];
+  if (static_cast<int>(blockIdx.x) == nb) {
+    __shared__ double sh[kCountThreads / 64][3];
+    if (st->done) return;
+    double a = 0.0, b = 0.0, c = 0.0;
+    for (int i = threadIdx.x; i < fin.count; i += kCountThreads) {
+      a += fin.part[3 * i + 0];
+      b += fin.part[3 * i + 1];
+      c += fin.part[3 * i + 2];
+    }
+    a = wave_sum(a);
+    b = wave_sum(b);
+    c = wave_sum(c);
+    if ((threadIdx.x & 63) == 0) {
+      sh[threadIdx.x >> 6][0] = a;
+      sh[threadIdx.x >> 6][1] = b;
+      sh[threadIdx.x >> 6][2] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      a = sh[0][0];
+      b = sh[0][1];
+      c = sh[0][2];
+      for (int w = 1; w < kCountThreads / 64; ++w) {
+        a += sh[w][0];
+        b += sh[w][1];
+        c += sh[w][2];
+      }
+      finalize_scalar(*fin.inst, iter - 1, a, b, c, 0.0, 0, fin.ndone, 1, fin.mirror);
+    }
+    return;
+  }
   if (st->done) return;
   const int I = blockIdx.x;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -775,10 +831,11 @@ hipError_t launch_bsr_index(const BsrMat& M, int nb, const BsrIndex& idx,
 hipError_t launch_bsr_symbolic(const BsrMat& A, int nb,
                                const BsrSymbolic& sym, const BsrMat& Q,
                                int32_t cap, BsrCounters* ctr,
-                               const DevState* st, int iter, hipStream_t s) {
+                               const DevState* st, int iter,
+                               const BsrScalar& fin, hipStream_t s) {
   const int nbw = (nb + 31) / 32;
-  hipLaunchKernelGGL(bsr_symbolic_count_kernel, dim3(nb), dim3(kCountThreads),
-                     0, s, A, nb, nbw, sym, ctr, st, iter);
+  hipLaunchKernelGGL(bsr_symbolic_count_kernel, dim3(nb + (fin.part ? 1 : 0)),
+                     dim3(kCountThreads), 0, s, A, nb, nbw, sym, ctr, st, iter, fin);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(bsr_symbolic_fill_kernel, dim3(nb), dim3(64), 0, s, sym,

@@ -251,6 +251,18 @@ hipError_t grow(sp2_ctx c, P*& ptr, size_t& cap, size_t bytes, hipStream_t s) {
   return e;
 }
 
+// Makes the pinned buffer of the outcomes hold at least `bytes`.
+hipError_t pin(sp2_ctx c, size_t bytes) {
+  if (bytes <= c->h_state_cap) return hipSuccess;
+  if (c->h_state) (void)hipHostFree(c->h_state);
+  c->h_state = nullptr;
+  c->h_state_cap = 0;
+  const hipError_t e =
+      hipHostMalloc(reinterpret_cast<void**>(&c->h_state), bytes, hipHostMallocDefault);
+  if (e == hipSuccess) c->h_state_cap = bytes;
+  return e;
+}
+
 sp2_status fail(sp2_ctx c, sp2_status s, const char* what, hipError_t e) {
   if (c) {
     c->err = what;
@@ -497,14 +509,7 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   c->run_solo = (count == 1);
   c->run_mb = plan.mb;
   c->run_grid = static_cast<int>(plan.seats.size());
-  const size_t hb = count * sizeof(DevState) + 256;
-  if (hb > c->h_state_cap) {
-    if (c->h_state) (void)hipHostFree(c->h_state);
-    c->h_state = nullptr;
-    c->h_state_cap = 0;
-    SP2_HIP(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_state), hb, hipHostMallocDefault));
-    c->h_state_cap = hb;
-  }
+  SP2_HIP(c, pin(c, count * sizeof(DevState) + 256));
   c->h_inst = inst;
   c->mcweeny = false;
   c->stretch = false;
@@ -990,8 +995,13 @@ sp2_status run_batch(sp2_ctx c) {
                               c->d_part_f0, s));
   }
   HostMirror* mirror = noalloc ? nullptr : c->mirror;
-  SP2_HIP(c, sp2::launch_finalize(c->d_inst, count, c->d_part, c->d_part_f0,
-                                  c->d_ndone, mirror, 0, s));
+  // block-sparse, Frobenius norm: the scalar step of a product runs beside
+  // the symbolic count of the next, one step later than as a launch of its own
+  const bool fused = c->bsr && c->opt.norm == SP2_NORM_FROBENIUS;
+  const int lookahead = fused ? kLookahead - 1 : kLookahead;
+  if (!fused)
+    SP2_HIP(c, sp2::launch_finalize(c->d_inst, count, c->d_part, c->d_part_f0,
+                                    c->d_ndone, mirror, 0, s));
   if (!noalloc) SP2_HIP(c, hipEventRecord(c->ev_ring[0], s));
 
   sp2::SquareArgs a;
@@ -1018,8 +1028,8 @@ sp2_status run_batch(sp2_ctx c) {
         if (nd >= count) break;
       }
     } else {
-      if (i > kLookahead)
-        SP2_HIP(c, hipEventSynchronize(c->ev_ring[(i - kLookahead) % kRing]));
+      if (i > lookahead)
+        SP2_HIP(c, hipEventSynchronize(c->ev_ring[(i - lookahead) % kRing]));
       if (__atomic_load_n(&c->mirror->all_done, __ATOMIC_ACQUIRE)) break;
     }
     a.iter = i;
@@ -1027,8 +1037,17 @@ sp2_status run_batch(sp2_ctx c) {
     if (c->bsr) {
       const sp2::BsrMat& cur = c->b.m[(i - 1) & 1];
       const sp2::BsrMat& nxt = c->b.m[i & 1];
+      sp2::BsrScalar fin{};
+      if (fused) {
+        const Instance& in = c->h_inst[0];
+        fin.inst = c->d_inst;
+        fin.part = (i == 1) ? c->d_part_f0 : c->d_part;
+        fin.count = (i == 1) ? in.nf0blk : in.ntiles;
+        fin.ndone = c->d_ndone;
+        fin.mirror = mirror;
+      }
       SP2_HIP(c, sp2::launch_bsr_symbolic(cur, c->b.nb, c->b.sym, nxt,
-                                          c->b.cap, c->b.ctr, c->d_st, i, s));
+                                          c->b.cap, c->b.ctr, c->d_st, i, fin, s));
       SP2_HIP(c, sp2::launch_bsr_numeric(cur, nxt, c->b.sym, c->b.ctr,
                                          c->d_inst, i,
                                          static_cast<int>(c->b.n), c->d_part,
@@ -1082,16 +1101,37 @@ sp2_status run_batch(sp2_ctx c) {
       }
       if (timing) SP2_HIP(c, hipEventRecord(c->ev_nm[2 * i + 1], s));
     }
-    SP2_HIP(c, sp2::launch_finalize(c->d_inst, count, c->d_part, c->d_part_f0,
-                                    c->d_ndone, mirror, i, s));
+    if (!fused)
+      SP2_HIP(c, sp2::launch_finalize(c->d_inst, count, c->d_part, c->d_part_f0,
+                                      c->d_ndone, mirror, i, s));
     if (!noalloc) SP2_HIP(c, hipEventRecord(c->ev_ring[i % kRing], s));
     last = i;
   }
+  // the last product's scalar step (nothing to do after a stop)
+  if (fused)
+    SP2_HIP(c, sp2::launch_finalize(c->d_inst, count, c->d_part, c->d_part_f0,
+                                    c->d_ndone, mirror, last, s));
   float ms = 0.f;
   if (!noalloc) {
     SP2_HIP(c, hipEventRecord(c->ev_stop, s));
     SP2_HIP(c, hipEventSynchronize(c->ev_stop));
     SP2_HIP(c, hipEventElapsedTime(&ms, c->ev_start, c->ev_stop));
+  }
+  // block-sparse: the counters and the steps' product counts come through
+  // pinned memory with the state, in one wait
+  const char* h_ctr = nullptr;
+  const uint32_t* h_prod = nullptr;
+  if (c->bsr) {
+    const size_t o1 = (sizeof(DevState) + 255) / 256 * 256;
+    const size_t o2 = o1 + (sizeof(sp2::BsrCounters) + 255) / 256 * 256;
+    const size_t pb = static_cast<size_t>(last + 1) * c->b.grid * sizeof(uint32_t);
+    SP2_HIP(c, pin(c, o2 + pb));
+    char* h = reinterpret_cast<char*>(c->h_state);
+    SP2_HIP(c, hipMemcpyAsync(h + o1, c->b.ctr, sizeof(sp2::BsrCounters),
+                              hipMemcpyDeviceToHost, s));
+    SP2_HIP(c, hipMemcpyAsync(h + o2, c->b.sym.prod_wg, pb, hipMemcpyDeviceToHost, s));
+    h_ctr = h + o1;
+    h_prod = reinterpret_cast<const uint32_t*>(h + o2);
   }
   c->host_state.resize(count);
   SP2_HIP(c, hipMemcpyAsync(c->host_state.data(), c->d_st,
@@ -1116,18 +1156,13 @@ sp2_status run_batch(sp2_ctx c) {
   c->run_ms = ms;
   if (c->bsr) {
     sp2::BsrCounters& ctr = c->b.host_ctr;
-    SP2_HIP(c, hipMemcpy(&ctr, c->b.ctr, sizeof(ctr), hipMemcpyDeviceToHost));
+    memcpy(&ctr, h_ctr, sizeof(ctr));
     // block products per step: the numeric workgroups' counts, summed here
-    const int nst = std::min(steps, c->opt.max_iter);
-    if (nst > 0) {
-      std::vector<uint32_t> pw(static_cast<size_t>(nst + 1) * c->b.grid);
-      SP2_HIP(c, hipMemcpy(pw.data(), c->b.sym.prod_wg, pw.size() * sizeof(uint32_t),
-                           hipMemcpyDeviceToHost));
-      for (int i = 1; i <= nst; ++i) {
-        unsigned long long t = 0;
-        for (int b = 0; b < c->b.grid; ++b) t += pw[static_cast<size_t>(i) * c->b.grid + b];
-        ctr.products[i] = t;
-      }
+    const int nst = std::min({steps, c->opt.max_iter, last});
+    for (int i = 1; i <= nst; ++i) {
+      unsigned long long t = 0;
+      for (int b = 0; b < c->b.grid; ++b) t += h_prod[static_cast<size_t>(i) * c->b.grid + b];
+      ctr.products[i] = t;
     }
     if (ctr.overflow & 1)
       return fail(c, SP2_OUT_OF_MEMORY,

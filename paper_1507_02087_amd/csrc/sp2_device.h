@@ -550,6 +550,16 @@ struct BsrCounters {
   unsigned long long products[kMaxIter + 2];
 };
 
+// The scalar step of the product before, taken beside the symbolic count
+// (Frobenius norm); part null: none.
+struct BsrScalar {
+  const Instance* inst;
+  const double* part;
+  int32_t count;        // triples in part
+  int32_t* ndone;
+  HostMirror* mirror;
+};
+
 hipError_t launch_bsr_reset(BsrCounters* ctr, hipStream_t s);
 // Index of the flagged blocks of M per row (extraction of the result).
 hipError_t launch_bsr_index(const BsrMat& M, int nb, const BsrIndex& idx,
@@ -559,7 +569,8 @@ hipError_t launch_bsr_index(const BsrMat& M, int nb, const BsrIndex& idx,
 hipError_t launch_bsr_symbolic(const BsrMat& A, int nb,
                                const BsrSymbolic& sym, const BsrMat& Q,
                                int32_t cap, BsrCounters* ctr,
-                               const DevState* st, int iter, hipStream_t s);
+                               const DevState* st, int iter,
+                               const BsrScalar& fin, hipStream_t s);
 hipError_t launch_bsr_numeric(const BsrMat& A, const BsrMat& B,
                               const BsrSymbolic& sym, BsrCounters* ctr,
                               const Instance* inst, int iter, int n,
