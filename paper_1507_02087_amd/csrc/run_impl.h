@@ -19,8 +19,8 @@
 //
 // Measured on one MI355X, us a step (launch sequence -> resident, floor = the
 // product at the rate of a large library product, 70 / 150 / 354 TFLOP/s):
-//   FP64  N = 100: 20.8 -> 10.0   1000: 61 -> 34 (14)   2500: 391 -> 276 (223)
-//         4096: 1122 -> 1090 (982)
+//   FP64  N = 100: 20.8 -> 10.0   1000: 61 -> 34 (14)   2500: 391 -> 286 (223)
+//         4096: 1122 -> 1101 (982)
 //   FP32  100: 23 -> 9.6   1000: 43 -> 24 (7)   1777: 99 -> 69 (37)
 //         3001: 290 -> 249 (180)   4000: 618 -> 528 (427)
 //   BF16x3  100: 23 -> 9.5   1000: 43 -> 22 (3)   2500: 99.7 -> 92.8 (44)
