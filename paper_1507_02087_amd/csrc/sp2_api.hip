@@ -200,6 +200,11 @@ struct sp2_ctx_s {
   const sp2::RunSeat* d_seats = nullptr;
   const int2* d_run_tiles = nullptr;
   const Instance* d_run_inst = nullptr;
+  // cleared when the device refuses a cooperative launch; the arguments of
+  // the method set since the init, for the set-up of the other driver
+  bool cooperative = true;
+  std::vector<double> set_mcw[2], set_acc[4];
+  int32_t set_accelerate = 0;
   std::vector<int> run_grids[3][2];   // co-resident workgroups per edge, by
                                       // precision and batch; found once
   bool run_solo = true;
@@ -412,7 +417,7 @@ int active_instances(sp2_ctx c) {
 // Whether a resident run is the better driver, and its plan.
 bool choose_resident(sp2_ctx c, sp2::RunPlan* plan) {
   const sp2_options& o = c->opt;
-  if (c->arena || o.launch != SP2_LAUNCH_AUTO || o.norm != SP2_NORM_FROBENIUS ||
+  if (c->arena || !c->cooperative || o.launch != SP2_LAUNCH_AUTO || o.norm != SP2_NORM_FROBENIUS ||
       o.kernel_config != 0 || o.tail_split != 0 || o.kernel_timing != 0)
     return false;
   // Sizes where it is: measured against the launch sequence, the resident
@@ -526,6 +531,8 @@ sp2_status setup(sp2_ctx c) {
   const size_t esz = c->fp64_store ? 8 : 4;
   hipStream_t s = c->stream;
   release_graph(c);
+  for (auto& v : c->set_mcw) v.clear();
+  for (auto& v : c->set_acc) v.clear();
   sp2::RunPlan plan;
   c->resident = choose_resident(c, &plan);
   if (c->resident) return setup_resident(c, plan);
@@ -895,7 +902,8 @@ sp2_status run_persistent(sp2_ctx c) {
 constexpr int kRunChainN = 1800;
 
 // One resident run: state reset, the cooperative launch, and the copy of the
-// states and the error word.
+// states and the error word. A refused launch clears c->cooperative and has
+// run nothing.
 sp2_status run_resident(sp2_ctx c) {
   const int count = static_cast<int>(c->hi.size());
   hipStream_t s = c->stream;
@@ -923,8 +931,15 @@ sp2_status run_resident(sp2_ctx c) {
   SP2_HIP(c, hipEventRecord(c->ev_start, s));
   SP2_HIP(c, sp2::launch_state_reset(c->d_st, count, c->d_ndone, err,
                                      static_cast<int>(words), s));
-  SP2_HIP(c, sp2::launch_run(c->opt.precision, c->run_mb, c->mcweeny, c->run_solo, a,
-                             c->run_grid, s));
+  const hipError_t launched = sp2::launch_run(c->opt.precision, c->run_mb, c->mcweeny,
+                                              c->run_solo, a, c->run_grid, s);
+  if (launched == hipErrorIllegalState || launched == hipErrorNotSupported ||
+      launched == hipErrorCooperativeLaunchTooLarge) {
+    (void)hipGetLastError();
+    c->cooperative = false;
+    return SP2_OK;
+  }
+  SP2_HIP(c, launched);
   SP2_HIP(c, hipEventRecord(c->ev_stop, s));
   SP2_HIP(c, hipMemcpyAsync(c->h_state, c->d_st,
                             count * sizeof(DevState) + sizeof(int32_t),
@@ -953,9 +968,35 @@ sp2_status run_resident(sp2_ctx c) {
 // no-allocation entry point (it has no pinned mirror and no events).
 constexpr int kNoAllocChunk = 4;
 
+// Sets the context up for the driver it has without cooperative launches
+// (the device gives them to one process at a time), with the method that was
+// set on the resident run.
+sp2_status leave_resident(sp2_ctx c) {
+  std::vector<double> mcw[2], acc[4];
+  for (int q = 0; q < 2; ++q) mcw[q].swap(c->set_mcw[q]);
+  for (int q = 0; q < 4; ++q) acc[q].swap(c->set_acc[q]);
+  const int32_t count = static_cast<int32_t>(c->hi.size());
+  c->inited = false;
+  sp2_status st = setup(c);
+  if (st != SP2_OK) return st;
+  c->inited = true;
+  if (!mcw[0].empty())
+    st = sp2_set_mcweeny(c, count, mcw[0].data(), mcw[1].empty() ? nullptr : mcw[1].data());
+  else if (!acc[0].empty())
+    st = sp2_set_homo_lumo(c, count, acc[0].data(), acc[1].data(), acc[2].data(),
+                           acc[3].data(), c->set_accelerate);
+  if (st != SP2_OK) c->inited = false;
+  return st;
+}
+
 sp2_status run_batch(sp2_ctx c) {
   SP2_HIP(c, hipSetDevice(c->device));
-  if (c->resident && !c->bsr) return run_resident(c);
+  if (c->resident && !c->bsr) {
+    sp2_status st = run_resident(c);
+    if (st != SP2_OK || c->cooperative) return st;
+    st = leave_resident(c);
+    if (st != SP2_OK) return st;
+  }
   if (c->persistent && !c->mcweeny && !c->bsr) return run_persistent(c);
   hipStream_t s = c->stream;
   const int count = static_cast<int>(c->hi.size());
@@ -1973,6 +2014,8 @@ sp2_status sp2_set_mcweeny(sp2_ctx c, int32_t count, const double* mu,
   for (const HostInst& h : c->hi)
     pool_elems = std::max(pool_elems,
                           h.xoff + static_cast<size_t>(h.np) * h.ld);
+  c->set_mcw[0].assign(mu, mu + count);
+  c->set_mcw[1].assign(xi ? xi : mu, xi ? xi + count : mu);
   const size_t esz = c->fp64_store ? 8 : 4;
   SP2_HIP(c, grow(c, c->s_pool, c->s_pool_cap, pool_elems * esz, s));
   const bool split = (c->opt.precision == SP2_BF16X3);
@@ -2108,6 +2151,9 @@ sp2_status sp2_set_homo_lumo(sp2_ctx c, int32_t count, const double* homo_out,
     }
   }
   hipStream_t s = c->stream;
+  const double* const set[4] = {homo_out, homo_in, lumo_in, lumo_out};
+  for (int q = 0; q < 4; ++q) c->set_acc[q].assign(set[q], set[q] + count);
+  c->set_accelerate = accelerate;
   const size_t abytes = alpha.size() * sizeof(double);
   SP2_HIP(c, grow(c, c->d_sched, c->d_sched_cap, abytes + pol.size(), s));
   c->h_sched_alpha = alpha;
