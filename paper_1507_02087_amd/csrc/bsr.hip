@@ -98,14 +98,17 @@ constexpr int kCountThreads = 256;
 // the product before (the finalize kernel's sums and finalize_scalar): the
 // pattern does not depend on it, and as a launch of its own it stood 5.3 us
 // of a 68 us step between two products. Its outcome is read by the kernels
-// after this one; a workgroup here that reads `done` as it is being set
-// counts a row that nobody uses, or does not.
+// after this one. A row workgroup may look at `done` while it is being set:
+// one thread reads it and shares it through LDS, so that all four waves count
+// the row (which nobody uses then) or none does. Waves that decided for
+// themselves could go on with LDS that an exited one never wrote.
 __global__ __launch_bounds__(kCountThreads) void bsr_symbolic_count_kernel(
     BsrMat A, int nb, int nbw, BsrSymbolic sym, BsrCounters* ctr,
     const DevState* st, int iter, BsrScalar fin) {
   __shared__ uint32_t bm[kMaxBlockCols / 32];
   __shared__ int32_t rk0[kCountThreads], pfx[kCountThreads + 1];
   __shared__ int32_t wsum[kCountThreads / 64];
+  __shared__ int32_t stopped;
   if (static_cast<int>(blockIdx.x) == nb) {
     __shared__ double sh[kCountThreads / 64][3];
     if (st->done) return;
@@ -137,12 +140,14 @@ __global__ __launch_bounds__(kCountThreads) void bsr_symbolic_count_kernel(
     }
     return;
   }
-  if (st->done) return;
   const int I = blockIdx.x;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (t == 0)
+    stopped = __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int w = t; w < nbw; w += kCountThreads) bm[w] = 0;
   const int b0 = A.row_ptr[I], b1 = A.row_ptr[I + 1];
   __syncthreads();
+  if (stopped) return;
   // the diagonal block is always kept: the identity term of a stretched
   // step (Alg. 4) writes it even where the iterate's block is empty
   if (t == 0) atomicOr(&bm[I >> 5], 1u << (I & 31));
