@@ -200,9 +200,14 @@ struct sp2_ctx_s {
   const sp2::RunSeat* d_seats = nullptr;
   const int2* d_run_tiles = nullptr;
   const Instance* d_run_inst = nullptr;
-  // cleared when the device refuses a cooperative launch; the arguments of
-  // the method set since the init, for the set-up of the other driver
-  bool cooperative = true;
+  // cleared when the device refuses a cooperative launch, or its workgroups
+  // wait for each other longer than run_wait_ms because other work holds the
+  // device (an error instead if wait_is_error: a limit that was asked for);
+  // the arguments of the method set since the init, for the set-up of the
+  // other driver
+  bool teams_ok = true;
+  bool wait_is_error = false;
+  long long run_wait_ms = 2000;
   std::vector<double> set_mcw[2], set_acc[4];
   int32_t set_accelerate = 0;
   std::vector<int> run_grids[3][2];   // co-resident workgroups per edge, by
@@ -417,7 +422,7 @@ int active_instances(sp2_ctx c) {
 // Whether a resident run is the better driver, and its plan.
 bool choose_resident(sp2_ctx c, sp2::RunPlan* plan) {
   const sp2_options& o = c->opt;
-  if (c->arena || !c->cooperative || o.launch != SP2_LAUNCH_AUTO || o.norm != SP2_NORM_FROBENIUS ||
+  if (c->arena || !c->teams_ok || o.launch != SP2_LAUNCH_AUTO || o.norm != SP2_NORM_FROBENIUS ||
       o.kernel_config != 0 || o.tail_split != 0 || o.kernel_timing != 0)
     return false;
   // Sizes where it is: measured against the launch sequence, the resident
@@ -643,7 +648,7 @@ sp2_status setup(sp2_ctx c) {
   // N = 4080, FP64 to 2816): a Lanczos step at N = 4000 takes 21 us from
   // there and 67 in chunks read from memory
   c->spec_run_grid = 0;
-  if (spectral && count == 1 && active_instances(c) == 1) {
+  if (spectral && c->teams_ok && count == 1 && active_instances(c) == 1) {
     c->spec_run_grid = sp2::spectral_resident_grid(
         c->fp64_store, static_cast<int>(c->hi[0].n), c->num_cus);
     if (c->spec_run_grid > 0) {
@@ -902,8 +907,9 @@ sp2_status run_persistent(sp2_ctx c) {
 constexpr int kRunChainN = 1800;
 
 // One resident run: state reset, the cooperative launch, and the copy of the
-// states and the error word. A refused launch clears c->cooperative and has
-// run nothing.
+// states and the error word. A launch that was refused, and has run nothing,
+// clears c->teams_ok; so does one whose teams did not meet in time, whose
+// iterates and states the other driver forms anew from F.
 sp2_status run_resident(sp2_ctx c) {
   const int count = static_cast<int>(c->hi.size());
   hipStream_t s = c->stream;
@@ -924,7 +930,7 @@ sp2_status run_resident(sp2_ctx c) {
   a.count = count;
   a.stretch = c->stretch ? 1 : 0;
   a.chain_n = kRunChainN;
-  a.wait_limit = c->wait_ms * c->wall_khz;
+  a.wait_limit = c->run_wait_ms * c->wall_khz;
   c->timed = false;
   c->square_ms.clear();
   c->norm_ms.clear();
@@ -936,7 +942,7 @@ sp2_status run_resident(sp2_ctx c) {
   if (launched == hipErrorIllegalState || launched == hipErrorNotSupported ||
       launched == hipErrorCooperativeLaunchTooLarge) {
     (void)hipGetLastError();
-    c->cooperative = false;
+    c->teams_ok = false;
     return SP2_OK;
   }
   SP2_HIP(c, launched);
@@ -947,10 +953,14 @@ sp2_status run_resident(sp2_ctx c) {
   SP2_HIP(c, hipStreamSynchronize(s));
   float ms = 0.f;
   SP2_HIP(c, hipEventElapsedTime(&ms, c->ev_start, c->ev_stop));
-  if (*reinterpret_cast<const int32_t*>(c->h_state + count) != 0)
-    return fail(c, SP2_HIP_ERROR,
-                "resident run: a workgroup waited for its team longer than "
-                "its limit", hipSuccess);
+  if (*reinterpret_cast<const int32_t*>(c->h_state + count) != 0) {
+    if (c->wait_is_error)
+      return fail(c, SP2_HIP_ERROR,
+                  "resident run: a workgroup waited for its team longer than "
+                  "its limit", hipSuccess);
+    c->teams_ok = false;
+    return SP2_OK;
+  }
   c->host_state.assign(c->h_state, c->h_state + count);
   int32_t steps = 0;
   for (const DevState& h : c->host_state) {
@@ -968,9 +978,10 @@ sp2_status run_resident(sp2_ctx c) {
 // no-allocation entry point (it has no pinned mirror and no events).
 constexpr int kNoAllocChunk = 4;
 
-// Sets the context up for the driver it has without cooperative launches
-// (the device gives them to one process at a time), with the method that was
-// set on the resident run.
+// Sets the context up for the driver it has without resident runs (the
+// device gives cooperative launches to one process at a time, and a team
+// whose members other work keeps off the device gives up), with the method
+// that was set on the resident run.
 sp2_status leave_resident(sp2_ctx c) {
   std::vector<double> mcw[2], acc[4];
   for (int q = 0; q < 2; ++q) mcw[q].swap(c->set_mcw[q]);
@@ -993,7 +1004,7 @@ sp2_status run_batch(sp2_ctx c) {
   SP2_HIP(c, hipSetDevice(c->device));
   if (c->resident && !c->bsr) {
     sp2_status st = run_resident(c);
-    if (st != SP2_OK || c->cooperative) return st;
+    if (st != SP2_OK || c->teams_ok) return st;
     st = leave_resident(c);
     if (st != SP2_OK) return st;
   }
@@ -1125,7 +1136,7 @@ sp2_status run_batch(sp2_ctx c) {
         ra.dots = ra.data + 2 * sp2::kSpecRunMax;
         ra.hist = ra.dots + 2 * sp2::kSpecRunMax;
         ra.iter = i;
-        ra.wait_limit = c->wait_ms * c->wall_khz;
+        ra.wait_limit = c->run_wait_ms * c->wall_khz;
         SP2_HIP(c, sp2::launch_spectral_resident(ra, c->fp64_store,
                                                  static_cast<int>(c->hi[0].n), c->num_cus,
                                                  c->spec_run_grid, s));
@@ -1183,10 +1194,16 @@ sp2_status run_batch(sp2_ctx c) {
     SP2_HIP(c, hipMemcpyAsync(&spec_err, c->d_spec_run_ctl + sp2::kSpecRunErr,
                               sizeof(spec_err), hipMemcpyDeviceToHost, s));
   SP2_HIP(c, hipStreamSynchronize(s));
-  if (spec_err != 0)
-    return fail(c, SP2_HIP_ERROR,
-                "spectral norm: a workgroup waited for the others longer than "
-                "its limit", hipSuccess);
+  if (spec_err != 0) {
+    if (c->wait_is_error)
+      return fail(c, SP2_HIP_ERROR,
+                  "spectral norm: a workgroup waited for the others longer than "
+                  "its limit", hipSuccess);
+    // again from F, with the chunked kernel, whose waits have no limit
+    c->teams_ok = false;
+    c->spec_run_grid = 0;
+    return run_batch(c);
+  }
   int32_t steps = 0;
   for (const DevState& h : c->host_state) {
     if (!h.done)
@@ -1444,12 +1461,23 @@ sp2_status sp2_create(sp2_ctx* out, int device, void* hip_stream) {
           hipSuccess && khz > 0)
     c->wall_khz = khz;
   // SP2_PERSIST_WAIT_MS: longest wait of a persistent workgroup for a queue
-  // item before the run gives up (milliseconds; default 2000)
-  if (const char* w = getenv("SP2_PERSIST_WAIT_MS")) {
+  // item, or of a resident one for its team, before the run fails
+  // (milliseconds; default 2000 for the queue). SP2_RESIDENT_WAIT_MS, and
+  // 2000 without either: longest wait for a team before the run changes over
+  // to the other driver.
+  auto ms_from = [](const char* name, long long* ms) {
+    const char* w = getenv(name);
     char* end = nullptr;
-    const long long v = strtoll(w, &end, 10);
-    if (end != w && v >= 0) c->wait_ms = v;
+    const long long v = w ? strtoll(w, &end, 10) : -1;
+    if (!w || end == w || v < 0) return false;
+    *ms = v;
+    return true;
+  };
+  if (ms_from("SP2_PERSIST_WAIT_MS", &c->wait_ms)) {
+    c->run_wait_ms = c->wait_ms;
+    c->wait_is_error = true;
   }
+  if (ms_from("SP2_RESIDENT_WAIT_MS", &c->run_wait_ms)) c->wait_is_error = false;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess &&
       prop.multiProcessorCount > 0)
