@@ -27,6 +27,22 @@ struct Plan {
 Plan make_plan(const std::vector<int>& slots, const std::vector<int>& owner,
                const std::vector<int>& nk, int concurrency, int tail_split);
 
+// FP64 resident runs past this N add up a wave's K part (a quarter of the K
+// range) as one chain, without a second set of sums: the launch sequence
+// adds the whole range as one chain there, so the result is still the more
+// accurate one (N = 4096: 5.0e-15 against 8.5e-15), and rounding further
+// below the resolution of the traces only delays the stop (ten runs at
+// N = 3001: 303 steps with the second set, 292 without, 291 in sequence).
+constexpr int kRunChainN = 1800;
+// Single runs up to this N have chains of three blocks (48 columns in FP32, 24
+// in FP64) at 32-tiles, and in FP32 at 48-tiles: the launch sequence splits
+// the K range of such an instance into up to 16 pieces, and with the chains
+// of the larger runs (9 or 12 blocks) errors were larger than its own (FP32
+// N = 700: 7.6e-7 against 4.9e-7, FP64 N = 280: 1.52e-15 against 1.31e-15; with
+// the short ones 4.2e-7 and 1.25e-15, and a step takes up to 1.5 % longer).
+// Past it the sequence has the longer chains, and so has a batch's queue.
+constexpr int kRunShortN = 1050;
+
 // Work plan of a resident run.
 struct RunInst {
   int64_t n = 0;

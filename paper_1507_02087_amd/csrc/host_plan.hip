@@ -124,6 +124,11 @@ RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edg
     const int cap =
         (count == 1 && precision != 0) ? std::min(grids[q], num_cus) : grids[q];
     if (cap < 1) continue;
+    // FP64 64-tiles leave no registers for the second set of sums, so a
+    // wave's K part is one chain; up to kRunChainN rows the launch sequence
+    // of a single run has shorter ones (N = 1225 to 1400: its errors were
+    // 1.15 to 1.19 times smaller). A batch's other driver never has.
+    if (count == 1 && precision == 0 && mb == 4 && inst[0].n <= kRunChainN) continue;
     std::vector<int64_t> tiles(count);
     std::vector<double> tile_us(count);
     int64_t total = 0;

@@ -3,19 +3,19 @@
 
 namespace sp2 {
 
-const void* run_kernel_f64(int mb, bool mw, bool solo);
-const void* run_kernel_f32(int mb, bool mw, bool solo);
-const void* run_kernel_b3(int mb, bool mw, bool solo);
+const void* run_kernel_f64(int mb, bool mw, RunKind kind);
+const void* run_kernel_f32(int mb, bool mw, RunKind kind);
+const void* run_kernel_b3(int mb, bool mw, RunKind kind);
 
 namespace {
 
 constexpr int kRunThreads = 256;
 
-const void* run_kernel_of(int precision, int mb, bool mw, bool solo) {
+const void* run_kernel_of(int precision, int mb, bool mw, RunKind kind) {
   switch (precision) {
-    case 0: return run_kernel_f64(mb, mw, solo);
-    case 1: return run_kernel_f32(mb, mw, solo);
-    default: return run_kernel_b3(mb, mw, solo);
+    case 0: return run_kernel_f64(mb, mw, kind);
+    case 1: return run_kernel_f32(mb, mw, kind);
+    default: return run_kernel_b3(mb, mw, kind);
   }
 }
 
@@ -26,8 +26,8 @@ const int* run_edges(int precision) {
   return precision == 0 ? f64 : (precision == 1 ? f32 : b3);
 }
 
-int run_max_grid(int precision, int mb, bool mw, bool solo, int num_cus) {
-  const void* fn = run_kernel_of(precision, mb, mw, solo);
+int run_max_grid(int precision, int mb, bool mw, RunKind kind, int num_cus) {
+  const void* fn = run_kernel_of(precision, mb, mw, kind);
   int per = 0;
   if (!fn ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, kRunThreads, 0) != hipSuccess)
@@ -35,9 +35,9 @@ int run_max_grid(int precision, int mb, bool mw, bool solo, int num_cus) {
   return per * num_cus;
 }
 
-hipError_t launch_run(int precision, int mb, bool mw, bool solo, const RunArgs& a, int grid,
+hipError_t launch_run(int precision, int mb, bool mw, RunKind kind, const RunArgs& a, int grid,
                       hipStream_t s) {
-  const void* fn = run_kernel_of(precision, mb, mw, solo);
+  const void* fn = run_kernel_of(precision, mb, mw, kind);
   if (!fn) return hipErrorInvalidValue;
   RunArgs arg = a;
   void* params[] = {&arg};

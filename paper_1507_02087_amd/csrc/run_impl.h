@@ -62,9 +62,10 @@ struct RunType<2> {
 };
 
 // Precision P, tiles of 16 MB rows, NW waves. SOLO: for single runs, one
-// workgroup per CU where that buys registers.
-template <int P_, int MB_, int NW_, bool SOLO>
+// workgroup per CU where that buys registers. BRIEF: with the short chains.
+template <int P_, int MB_, int NW_, bool SOLO, bool BRIEF_ = false>
 struct RunCfg {
+  static constexpr bool BRIEF = BRIEF_;
   static constexpr int P = P_, MB = MB_, NW = NW_;
   using T = typename RunType<P>::T;
   using Vec = typename RunType<P>::Vec;
@@ -102,6 +103,9 @@ struct RunCfg {
   // grows with the chain and not with the wave's whole K part
   static constexpr bool TWO = (P == 0) ? MB <= 3 : P == 1;
   static constexpr int CHAIN = (8 + DEPTH - 1) / DEPTH * DEPTH;   // blocks
+  // or, in the kernels of small single runs (kRunShortN), after three
+  static constexpr int SHORT = 3;
+  static_assert(!BRIEF || (TWO && DEPTH % SHORT == 0), "whole chains per round");
   struct Acc {
     AccV c[MB][MB];
   };
@@ -219,20 +223,30 @@ __device__ __forceinline__ void run_main(const RunTile<C>& tile, RunSet<C> (&o)[
   };
   constexpr int D = C::DEPTH;
   int k = k0;
-  auto rounds = [&](int end) {
+  // f(d) after the products of set d
+  auto rounds = [&](int end, auto f) {
     for (; k + D <= end; k += D) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
         mma(o[d]);
         tile.load(o[d], k + d + D);
         __builtin_amdgcn_sched_barrier(0);
+        f(d);
       }
     }
   };
+  auto rest = [&](auto f) {
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (k + d < k1) {
+        mma(o[d]);
+        f(d);
+      }
+  };
+  auto none = [](int) {};
   if constexpr (C::TWO) {
     typename C::Acc sum = acc;
-    while (k1 - k > chain) {
-      rounds(k + chain);
+    auto flush = [&]() {
 #pragma unroll
       for (int m = 0; m < MB; ++m)
 #pragma unroll
@@ -241,20 +255,28 @@ __device__ __forceinline__ void run_main(const RunTile<C>& tile, RunSet<C> (&o)[
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc.c[m][n][j] = 0;
         }
+    };
+    if constexpr (C::BRIEF) {
+      auto each = [&](int d) {
+        if ((d + 1) % C::SHORT == 0) flush();
+      };
+      rounds(k1, each);
+      rest(each);
+    } else {
+      while (k1 - k > chain) {
+        rounds(k + chain, none);
+        flush();
+      }
+      rounds(k1, none);
+      rest(none);
     }
-    rounds(k1);
-#pragma unroll
-    for (int d = 0; d < D - 1; ++d)
-      if (k + d < k1) mma(o[d]);
 #pragma unroll
     for (int m = 0; m < MB; ++m)
 #pragma unroll
       for (int n = 0; n < MB; ++n) acc.c[m][n] += sum.c[m][n];
   } else {
-    rounds(k1);
-#pragma unroll
-    for (int d = 0; d < D - 1; ++d)
-      if (k + d < k1) mma(o[d]);
+    rounds(k1, none);
+    rest(none);
   }
 }
 

@@ -210,9 +210,9 @@ struct sp2_ctx_s {
   long long run_wait_ms = 2000;
   std::vector<double> set_mcw[2], set_acc[4];
   int32_t set_accelerate = 0;
-  std::vector<int> run_grids[3][2];   // co-resident workgroups per edge, by
-                                      // precision and batch; found once
-  bool run_solo = true;
+  std::vector<int> run_grids[3][3];   // co-resident workgroups per edge, by
+                                      // precision and kind; found once
+  sp2::RunKind run_kind = sp2::kRunSolo;
   int run_teams = 0, run_npull = 0;
   const int32_t* d_run_pull = nullptr;
   sp2::CopyJob* d_jobs = nullptr;
@@ -394,14 +394,20 @@ void release_groups(sp2_ctx c) {
 
 // Co-resident workgroups of the resident run for every tile edge of the
 // context's precision (with and without McWeeny, which uses the same plan).
-const std::vector<int>& run_grids(sp2_ctx c, bool solo) {
-  std::vector<int>& g = c->run_grids[c->opt.precision][solo ? 1 : 0];
+const std::vector<int>& run_grids(sp2_ctx c, sp2::RunKind kind) {
+  std::vector<int>& g = c->run_grids[c->opt.precision][kind];
   if (g.empty())
     for (const int* e = sp2::run_edges(c->opt.precision); *e; ++e)
       g.push_back(std::min(
-          sp2::run_max_grid(c->opt.precision, *e, false, solo, c->num_cus),
-          sp2::run_max_grid(c->opt.precision, *e, true, solo, c->num_cus)));
+          sp2::run_max_grid(c->opt.precision, *e, false, kind, c->num_cus),
+          sp2::run_max_grid(c->opt.precision, *e, true, kind, c->num_cus)));
   return g;
+}
+
+// The resident kernels of the context's instances.
+sp2::RunKind run_kind(sp2_ctx c) {
+  if (c->hi.size() > 1) return sp2::kRunBatch;
+  return c->hi[0].n <= sp2::kRunShortN ? sp2::kRunBrief : sp2::kRunSolo;
 }
 
 // Words of a resident run's exchange, cleared before it: the error word and
@@ -434,9 +440,8 @@ bool choose_resident(sp2_ctx c, sp2::RunPlan* plan) {
   for (const HostInst& h : c->hi)
     if (h.n > most) return false;
   for (const HostInst& h : c->hi) inst.push_back(sp2::RunInst{h.n, h.n_occ == 0 || h.n_occ == h.n});
-  const bool solo = inst.size() == 1;
   *plan = sp2::plan_run(inst, o.precision, sp2::run_edges(o.precision),
-                        run_grids(c, solo), c->num_cus);
+                        run_grids(c, run_kind(c)), c->num_cus);
   return plan->mb != 0;
 }
 
@@ -516,7 +521,7 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   c->d_run_pull = reinterpret_cast<const int32_t*>(base + ib + sb + tb);
   c->run_npull = static_cast<int>(plan.pull.size());
   c->run_teams = plan.teams;
-  c->run_solo = (count == 1);
+  c->run_kind = run_kind(c);
   c->run_mb = plan.mb;
   c->run_grid = static_cast<int>(plan.seats.size());
   SP2_HIP(c, pin(c, count * sizeof(DevState) + 256));
@@ -898,14 +903,6 @@ sp2_status run_persistent(sp2_ctx c) {
   return SP2_OK;
 }
 
-// FP64 resident runs past this N add up a wave's K part (a quarter of the K
-// range) as one chain, without a second set of sums: the launch sequence
-// adds the whole range as one chain there, so the result is still the more
-// accurate one (N = 4096: 5.0e-15 against 8.5e-15), and rounding further
-// below the resolution of the traces only delays the stop (ten runs at
-// N = 3001: 303 steps with the second set, 292 without, 291 in sequence).
-constexpr int kRunChainN = 1800;
-
 // One resident run: state reset, the cooperative launch, and the copy of the
 // states and the error word. A launch that was refused, and has run nothing,
 // clears c->teams_ok; so does one whose teams did not meet in time, whose
@@ -929,7 +926,7 @@ sp2_status run_resident(sp2_ctx c) {
   a.ndone = c->d_ndone;
   a.count = count;
   a.stretch = c->stretch ? 1 : 0;
-  a.chain_n = kRunChainN;
+  a.chain_n = sp2::kRunChainN;
   a.wait_limit = c->run_wait_ms * c->wall_khz;
   c->timed = false;
   c->square_ms.clear();
@@ -938,7 +935,7 @@ sp2_status run_resident(sp2_ctx c) {
   SP2_HIP(c, sp2::launch_state_reset(c->d_st, count, c->d_ndone, err,
                                      static_cast<int>(words), s));
   const hipError_t launched = sp2::launch_run(c->opt.precision, c->run_mb, c->mcweeny,
-                                              c->run_solo, a, c->run_grid, s);
+                                              c->run_kind, a, c->run_grid, s);
   if (launched == hipErrorIllegalState || launched == hipErrorNotSupported ||
       launched == hipErrorCooperativeLaunchTooLarge) {
     (void)hipGetLastError();

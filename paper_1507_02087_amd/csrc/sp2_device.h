@@ -379,13 +379,15 @@ struct RunArgs {
   int32_t chain_n;        // FP64: N past which a wave's K part is one chain
   long long wait_limit;   // constant-clock ticks of a team's longest wait
 };
+// The kernels of batches, of single runs, and of single runs of up to
+// kRunShortN rows (host_plan.h).
+enum RunKind { kRunBatch, kRunSolo, kRunBrief };
 // Tile edges, in units of 16 rows, that a precision's resident run is
 // compiled for, smallest first, ended by 0.
 const int* run_edges(int precision);
 // Workgroups of the resident run that fit on the device at once (0: none).
-// `solo`: the kernel of single runs, else that of batches.
-int run_max_grid(int precision, int mb, bool mw, bool solo, int num_cus);
-hipError_t launch_run(int precision, int mb, bool mw, bool solo, const RunArgs& a, int grid,
+int run_max_grid(int precision, int mb, bool mw, RunKind kind, int num_cus);
+hipError_t launch_run(int precision, int mb, bool mw, RunKind kind, const RunArgs& a, int grid,
                       hipStream_t s);
 // D = (X - c I) / a from an iterate in operand order; `symmetric` reads the
 // upper triangle only.
