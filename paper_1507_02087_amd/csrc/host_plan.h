@@ -58,6 +58,10 @@ struct RunPlan {
   double step_us = 0.0;          // estimated time of one product
 };
 
+// Whether the resident run is the faster driver of a batch: against the queue,
+// or with `mcweeny` (two products a step) against the launch sequence.
+bool resident_batch_pays(const std::vector<RunInst>& inst, int precision, bool mcweeny);
+
 // Seats for every instance of the batch on a device that holds `grid`
 // workgroups of `num_cus` CUs at once (grid(mb): their number for a tile
 // edge), with the tile edge (of `edges`, ended by 0) that the cost model

@@ -107,6 +107,57 @@ constexpr double kRunMeetUs = 8.0;
 
 }  // namespace
 
+// Measured on 32 to 6144 rows and 2 to 2048 instances, equal and mixed (time of
+// a step, resident over other driver). The other drivers' 128-tiles need
+// many large instances to fill the device, and waste what they pad; then
+// they are the faster ones, because an element of theirs is fetched half as
+// often as one of a 32- to 64-tile, and the teams of several large
+// instances evict each other's iterates from the L2s. `work` is the sum of
+// N^2 (tiles), `padded` the same over whole 128-tiles.
+//   One large instance with small ones as a single run; two: 0.3 to 0.99
+//             (BF16x3 2 x 3500: 1.01, McWeeny 2500: 1.04)
+//   FP64      (whole runs: the more accurate sums stop some steps later)
+//             256 x 600: 0.97, 32 x 700: 1.14, 16 x 1000: 0.98, 64: 1.09, 64 x 1500: 1.14, 8 x 1750: 1.07,
+//             4 x 2000: 1.08, 8 x 3000: 1.15; 256 of 64 to 1024 rows (padded 1.2): 0.74,
+//             64 of 200 to 1500 (1.14): 0.93
+//     McWeeny 16 x 500: 0.72, 32: 1.09, 16 x 1750: 0.93, 32: 1.01, 128 x 100: 1.07
+//   FP32      128 x 1000: 0.99, 512: 1.08, 64 x 2000: 0.97, 128: 1.05, 3 x 3000: 1.05,
+//             512 of 64 to 1024 rows (padded 1.19): 0.84
+//     McWeeny 128 x 1000: 1.00, 512: 1.11, 64 x 1500: 1.00, 4 x 2000: 1.16
+//   BF16x3    2048 x 500: 0.97, 32 x 1000: 0.92, 64: 1.04, 1024: 1.79, 6 x 1500: 0.81,
+//             8: 1.03, 4 x 2000: 1.02, 8 x 3500: 1.75; 512 of 64 to 1024 rows: 0.90
+//     McWeeny 256 x 200: 0.61, 1024: 1.06, 32 x 750: 0.80, 64: 1.18, 6 x 1250: 0.94,
+//             8: 1.20, 3 x 2000: 1.19
+bool resident_batch_pays(const std::vector<RunInst>& inst, int precision, bool mcweeny) {
+  int64_t most = 0, active = 0;
+  double work = 0.0, padded = 0.0;
+  for (const RunInst& i : inst) {
+    if (i.trivial) continue;
+    const double n = static_cast<double>(i.n), p = static_cast<double>((i.n + 127) / 128 * 128);
+    ++active;
+    most = std::max(most, i.n);
+    work += n * n;
+    padded += p * p;
+  }
+  const double m2 = static_cast<double>(most) * static_cast<double>(most);
+  if (work <= 1.2 * m2) return true;   // as a single run
+  if (work <= 2.05 * m2) return precision != 2 || most <= (mcweeny ? 2200 : 3000);
+  if (precision == 0) {
+    const bool mixed = padded >= 1.115 * work && work <= 0.7 * m2 * static_cast<double>(active);
+    if (!mcweeny)
+      return most <= 600 || (most <= 1750 && (active <= 16 || (mixed && work <= 200e6)));
+    return most <= 32 || (most <= 1750 && active <= (most <= 100 ? 64 : 16));
+  }
+  if (precision == 1) {
+    const bool fits = work <= (mcweeny ? 125e6 : 150e6) || padded >= 1.1 * work;
+    return most <= (mcweeny ? 1500 : 2000) && fits;
+  }
+  if (mcweeny)
+    return most <= 160 || work <= (most <= 450 ? 40e6 : (most <= 1100 ? 20e6 : 9.4e6));
+  return most <= 600 || work <= (most <= 1100 ? 36e6 : 15e6) ||
+         (most <= 1100 && padded >= 1.15 * work && work <= 200e6);
+}
+
 RunPlan plan_run(const std::vector<RunInst>& inst, int precision, const int* edges,
                  const std::vector<int>& grids, int num_cus) {
   const int count = static_cast<int>(inst.size());

@@ -425,21 +425,29 @@ int active_instances(sp2_ctx c) {
   return active;
 }
 
+std::vector<sp2::RunInst> run_instances(sp2_ctx c) {
+  std::vector<sp2::RunInst> inst;
+  for (const HostInst& h : c->hi)
+    inst.push_back(sp2::RunInst{h.n, h.n_occ == 0 || h.n_occ == h.n});
+  return inst;
+}
+
 // Whether a resident run is the better driver, and its plan.
 bool choose_resident(sp2_ctx c, sp2::RunPlan* plan) {
   const sp2_options& o = c->opt;
   if (c->arena || !c->teams_ok || o.launch != SP2_LAUNCH_AUTO || o.norm != SP2_NORM_FROBENIUS ||
       o.kernel_config != 0 || o.tail_split != 0 || o.kernel_timing != 0)
     return false;
-  // Sizes where it is: measured against the launch sequence, the resident
-  // step is the faster one at every N up to these (FP64 8192: equal; FP32
-  // 6144: 1853 us a step against 1892; BF16x3 3500: 188 against 199, 4096:
-  // equal, 5600: 742 against 510, where the sequence's 256-tiles take over).
+  // Sizes where it is: measured on single runs against the launch sequence,
+  // the resident step is the faster one at every N up to these (FP64 8192:
+  // equal; FP32 6144: 1853 us a step against 1892; BF16x3 3500: 188 against
+  // 199, 4096: equal, 5600: 742 against 510, where the sequence's 256-tiles
+  // take over). Batches: resident_batch_pays.
   const int64_t most = (o.precision == SP2_BF16X3) ? 3584 : 6144;
-  std::vector<sp2::RunInst> inst;
   for (const HostInst& h : c->hi)
     if (h.n > most) return false;
-  for (const HostInst& h : c->hi) inst.push_back(sp2::RunInst{h.n, h.n_occ == 0 || h.n_occ == h.n});
+  const std::vector<sp2::RunInst> inst = run_instances(c);
+  if (inst.size() > 1 && !sp2::resident_batch_pays(inst, o.precision, false)) return false;
   *plan = sp2::plan_run(inst, o.precision, sp2::run_edges(o.precision),
                         run_grids(c, run_kind(c)), c->num_cus);
   return plan->mb != 0;
@@ -535,8 +543,9 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
 }
 
 // Builds the instance table, tile table, launch groups and their plans, and
-// (re)allocates every workspace. Instances come in c->hi.
-sp2_status setup(sp2_ctx c) {
+// (re)allocates every workspace. Instances come in c->hi. Without
+// `resident`, for the driver that the context has beside resident runs.
+sp2_status setup(sp2_ctx c, bool resident = true) {
   const int count = static_cast<int>(c->hi.size());
   const size_t esz = c->fp64_store ? 8 : 4;
   hipStream_t s = c->stream;
@@ -544,7 +553,7 @@ sp2_status setup(sp2_ctx c) {
   for (auto& v : c->set_mcw) v.clear();
   for (auto& v : c->set_acc) v.clear();
   sp2::RunPlan plan;
-  c->resident = choose_resident(c, &plan);
+  c->resident = resident && choose_resident(c, &plan);
   if (c->resident) return setup_resident(c, plan);
   // configurations, padding, pool offsets
   auto choose = [&](int64_t n) { return library_config(c, n); };
@@ -2034,6 +2043,13 @@ sp2_status sp2_set_mcweeny(sp2_ctx c, int32_t count, const double* mu,
     }
   }
   SP2_HIP(c, hipSetDevice(c->device));
+  if (c->resident && count > 1 &&
+      !sp2::resident_batch_pays(run_instances(c), c->opt.precision, true)) {
+    c->inited = false;
+    const sp2_status st = setup(c, false);
+    if (st != SP2_OK) return st;
+    c->inited = true;
+  }
   hipStream_t s = c->stream;
   size_t pool_elems = 0;
   for (const HostInst& h : c->hi)
