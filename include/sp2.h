@@ -118,8 +118,9 @@ typedef enum {
                                 and kernel_config, tail_split and
                                 kernel_timing 0, a resident run where the
                                 library's cost model finds it the faster
-                                driver: one cooperative launch for the whole
-                                run (affine start, every step, the stop) in
+                                driver: one launch for the whole run (a
+                                cooperative one unless it is small; affine
+                                start, every step, the stop) in
                                 which each instance has a team of workgroups
                                 (of its own, or one that works through a list
                                 of instances), with square kernels of its own.

@@ -41,6 +41,7 @@ hipError_t launch_run(int precision, int mb, bool mw, RunKind kind, const RunArg
   if (!fn) return hipErrorInvalidValue;
   RunArgs arg = a;
   void* params[] = {&arg};
+  if (a.members > 0) return hipLaunchKernel(fn, dim3(grid), dim3(kRunThreads), params, 0, s);
   return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kRunThreads), params, 0, s);
 }
 

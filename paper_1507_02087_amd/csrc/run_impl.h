@@ -512,6 +512,28 @@ __device__ __forceinline__ int run_wait(const int32_t* w, int want, int32_t* err
   }
 }
 
+// The gate of an ordinary launch, which the device does not promise to place
+// as a whole: open once every workgroup has arrived, shut by the first that
+// waits too long (the others may wait for room that a run like this one
+// holds). Nothing has been done before it, so a shut run can be launched anew.
+__device__ __forceinline__ int run_gate(int32_t* gate, int members, long long limit) {
+  int free = 0;
+  const int k = __hip_atomic_fetch_add(gate, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (k == members - 1)
+    __hip_atomic_compare_exchange_strong(gate + 1, &free, kGateOpen, __ATOMIC_RELAXED,
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const long long t0 = wall_clock64();
+  for (;;) {
+    const int g = __hip_atomic_load(gate + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (g != 0) return g;
+    if (wall_clock64() - t0 > limit) {
+      free = 0;
+      __hip_atomic_compare_exchange_strong(gate + 1, &free, kGateShut, __ATOMIC_RELAXED,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
 // What a workgroup tells its team's first: its partial sums and the number
 // of the phase they belong to.
 __device__ __forceinline__ double run_peek(const double* p) {
@@ -528,6 +550,13 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES) void run_kernel(RunArgs a) {
   const int rank = seat->rank, size = seat->size, base = seat->base, team = seat->team;
   if (size == 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = run_uni(tid >> 6);
+  if (a.members > 0) {
+    if (tid == 0) word = run_gate(a.gate, a.members, a.gate_limit);
+    __syncthreads();
+    const int g = word;
+    __syncthreads();   // word may be rewritten only after every read
+    if (g != kGateOpen) return;
+  }
   const bool affine = a.stretch != 0;
   double* const ec = a.coef + 8 * team;   // StepCoef of the next product
   int32_t* const flag = a.flag + 32 * team;

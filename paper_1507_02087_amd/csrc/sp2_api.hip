@@ -214,6 +214,10 @@ struct sp2_ctx_s {
                                       // precision and kind; found once
   sp2::RunKind run_kind = sp2::kRunSolo;
   int run_teams = 0, run_npull = 0;
+  int run_members = 0;             // workgroups of an ordinary launch (0:
+                                   // cooperative)
+  bool gate_ok = true;             // cleared once a gate was shut
+  long long gate_ticks = 0;        // longest wait at a gate
   const int32_t* d_run_pull = nullptr;
   sp2::CopyJob* d_jobs = nullptr;
   size_t d_jobs_cap = 0;
@@ -410,8 +414,8 @@ sp2::RunKind run_kind(sp2_ctx c) {
   return c->hi[0].n <= sp2::kRunShortN ? sp2::kRunBrief : sp2::kRunSolo;
 }
 
-// Words of a resident run's exchange, cleared before it: the error word and
-// the next instance of the list, a line per team's release word, then the
+// Words of a resident run's exchange, cleared before it: the error word, the
+// next instance of the list and the gate, a line per team's release word, then the
 // seats' posts.
 size_t run_sync_words(int teams, size_t seats) {
   return 32 * (static_cast<size_t>(teams) + 1) +
@@ -475,7 +479,7 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   if (split)
     for (int q = 0; q < 4; ++q)
       SP2_HIP(c, grow(c, c->split_pool[q], c->split_cap[q], pool_elems * 2, s));
-  // behind the states: the error word (one copy brings both), the teams'
+  // behind the states: the control words (one copy brings both), the teams'
   // release words, the posts of the seats and the coefficients
   SP2_HIP(c, grow(c, c->d_st, c->d_st_cap,
                   count * sizeof(DevState) +
@@ -532,6 +536,16 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   c->run_kind = run_kind(c);
   c->run_mb = plan.mb;
   c->run_grid = static_cast<int>(plan.seats.size());
+  // Cooperative launches take turns, so that several threads' small runs lost
+  // the overlap that their launch sequences had. A single team of at most half
+  // as many workgroups as CUs (four hardware queues then fit the device) is
+  // launched as an ordinary kernel with a gate. us a run, 8 threads, sequence |
+  // cooperative | ordinary: FP64 N = 64 228 | 254 | 67, 300 312 | 321 | 107, FP32
+  // N = 400 314 | 279 | 97; one thread, FP64 N = 64: 647 | 301 | 279. Larger runs
+  // fill the device by themselves (FP64 N = 1000, 8 threads: 1236 | 917).
+  int members = 0;
+  for (const sp2::RunSeat& seat : plan.seats) members += seat.size > 0 ? 1 : 0;
+  c->run_members = (count == 1 && 2 * members <= c->num_cus) ? members : 0;
   SP2_HIP(c, pin(c, count * sizeof(DevState) + 256));
   c->h_inst = inst;
   c->mcweeny = false;
@@ -912,8 +926,8 @@ sp2_status run_persistent(sp2_ctx c) {
   return SP2_OK;
 }
 
-// One resident run: state reset, the cooperative launch, and the copy of the
-// states and the error word. A launch that was refused, and has run nothing,
+// One resident run: state reset, the launch, and the copy of the
+// states and the control words. A launch that was refused, and has run nothing,
 // clears c->teams_ok; so does one whose teams did not meet in time, whose
 // iterates and states the other driver forms anew from F.
 sp2_status run_resident(sp2_ctx c) {
@@ -937,6 +951,9 @@ sp2_status run_resident(sp2_ctx c) {
   a.stretch = c->stretch ? 1 : 0;
   a.chain_n = sp2::kRunChainN;
   a.wait_limit = c->run_wait_ms * c->wall_khz;
+  a.gate = err + 2;
+  a.gate_limit = c->gate_ticks;
+  a.members = c->gate_ok ? c->run_members : 0;
   c->timed = false;
   c->square_ms.clear();
   c->norm_ms.clear();
@@ -954,12 +971,17 @@ sp2_status run_resident(sp2_ctx c) {
   SP2_HIP(c, launched);
   SP2_HIP(c, hipEventRecord(c->ev_stop, s));
   SP2_HIP(c, hipMemcpyAsync(c->h_state, c->d_st,
-                            count * sizeof(DevState) + sizeof(int32_t),
+                            count * sizeof(DevState) + 4 * sizeof(int32_t),
                             hipMemcpyDeviceToHost, s));
   SP2_HIP(c, hipStreamSynchronize(s));
+  const int32_t* const word = reinterpret_cast<const int32_t*>(c->h_state + count);
+  if (a.members > 0 && word[3] != sp2::kGateOpen) {
+    c->gate_ok = false;
+    return run_resident(c);   // as a cooperative launch
+  }
   float ms = 0.f;
   SP2_HIP(c, hipEventElapsedTime(&ms, c->ev_start, c->ev_stop));
-  if (*reinterpret_cast<const int32_t*>(c->h_state + count) != 0) {
+  if (word[0] != 0) {
     if (c->wait_is_error)
       return fail(c, SP2_HIP_ERROR,
                   "resident run: a workgroup waited for its team longer than "
@@ -1484,6 +1506,11 @@ sp2_status sp2_create(sp2_ctx* out, int device, void* hip_stream) {
     c->wait_is_error = true;
   }
   if (ms_from("SP2_RESIDENT_WAIT_MS", &c->run_wait_ms)) c->wait_is_error = false;
+  // SP2_GATE_WAIT_MS: longest wait for the workgroups of a small resident run
+  // to arrive, before it is launched cooperatively (default 1)
+  long long gate_ms = 1;
+  (void)ms_from("SP2_GATE_WAIT_MS", &gate_ms);
+  c->gate_ticks = gate_ms * c->wall_khz;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess &&
       prop.multiProcessorCount > 0)

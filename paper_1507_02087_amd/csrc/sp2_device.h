@@ -378,7 +378,12 @@ struct RunArgs {
   int32_t stretch;        // the run stretches the matrices it squares
   int32_t chain_n;        // FP64: N past which a wave's K part is one chain
   long long wait_limit;   // constant-clock ticks of a team's longest wait
+  int32_t* gate;          // ordinary launch: [0] workgroups that have arrived,
+                          // [1] kGateOpen or kGateShut; zero at launch
+  int32_t members;        // ordinary launch: workgroups that arrive; else 0
+  long long gate_limit;   // ticks of the wait at the gate
 };
+constexpr int kGateOpen = 1, kGateShut = 2;
 // The kernels of batches, of single runs, and of single runs of up to
 // kRunShortN rows (host_plan.h).
 enum RunKind { kRunBatch, kRunSolo, kRunBrief };
@@ -387,6 +392,7 @@ enum RunKind { kRunBatch, kRunSolo, kRunBrief };
 const int* run_edges(int precision);
 // Workgroups of the resident run that fit on the device at once (0: none).
 int run_max_grid(int precision, int mb, bool mw, RunKind kind, int num_cus);
+// Cooperative, or with a.members > 0 an ordinary launch.
 hipError_t launch_run(int precision, int mb, bool mw, RunKind kind, const RunArgs& a, int grid,
                       hipStream_t s);
 // D = (X - c I) / a from an iterate in operand order; `symmetric` reads the
