@@ -74,7 +74,8 @@ __device__ __forceinline__ void post(double* p, double v) {
 // dependent fused multiply-add a row where the pivots of sturm_below take a
 // division. A zero minor has the sign opposite to the one before it. Rows are
 // taken in blocks of eight, read from LDS ahead of their chain; rows past the
-// order (a = 2, b2 = 0) keep the sign. The minors shrink by at most some 2^-50
+// order (a = 2, b2 = 0) keep the sign, and a zero that follows a zero there
+// (x is an eigenvalue) counts nothing more. The minors shrink by at most some 2^-50
 // a row, so a rescale every block keeps them in range.
 __device__ __forceinline__ int minors_below(const double* a, const double* b2, int blocks,
                                             double x) {
@@ -101,7 +102,7 @@ __device__ __forceinline__ int minors_below(const double* a, const double* b2, i
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const double p2 = fma(d[e], p1, -b[e] * p0);
-      const bool ng = (p2 == 0.0) ? !neg : p2 < 0.0;
+      const bool ng = (p2 == 0.0) ? (p1 == 0.0) == neg : p2 < 0.0;
       cnt += (ng != neg) ? 1 : 0;
       neg = ng;
       p0 = p1;
