@@ -124,10 +124,12 @@ typedef enum {
                                 which each instance has a team of workgroups
                                 (of its own, or one that works through a list
                                 of instances), with square kernels of its own.
-                                If the device refuses the launch, or other
-                                work keeps a team from meeting for 2 s, the
-                                run is done by the other driver, and so are
-                                all later ones of the context.
+                                Work on other streams and of other processes
+                                waits for such a run as a whole. If the device
+                                has no room for it, or other work keeps a team
+                                from meeting for 2 s, the run is done by the
+                                other driver, and so are all later ones of
+                                the context.
                                 Otherwise persistent for a batch of more than
                                 one instance with the Frobenius norm (Alg. 2
                                 or SP2-ACC), else a launch sequence per

@@ -200,9 +200,10 @@ struct sp2_ctx_s {
   const sp2::RunSeat* d_seats = nullptr;
   const int2* d_run_tiles = nullptr;
   const Instance* d_run_inst = nullptr;
-  // cleared when the device refuses a cooperative launch, or its workgroups
-  // wait for each other longer than run_wait_ms because other work holds the
-  // device (an error instead if wait_is_error: a limit that was asked for);
+  // cleared when the device gives a resident run no room (see run_resident),
+  // or its workgroups wait for each other longer than run_wait_ms because
+  // other work holds the device (an error instead if wait_is_error: a limit
+  // that was asked for);
   // the arguments of the method set since the init, for the set-up of the
   // other driver
   bool teams_ok = true;
@@ -214,9 +215,10 @@ struct sp2_ctx_s {
                                       // precision and kind; found once
   sp2::RunKind run_kind = sp2::kRunSolo;
   int run_teams = 0, run_npull = 0;
-  int run_members = 0;             // workgroups of an ordinary launch (0:
-                                   // cooperative)
-  bool gate_ok = true;             // cleared once a gate was shut
+  int run_members = 0;             // workgroups that have a seat
+  bool run_small = false;          // an ordinary launch is the better one
+  bool gate_ok = true;             // cleared once a small run's gate was shut
+  bool refused = false;            // cooperative launches go to another process
   long long gate_ticks = 0;        // longest wait at a gate
   const int32_t* d_run_pull = nullptr;
   sp2::CopyJob* d_jobs = nullptr;
@@ -543,9 +545,9 @@ sp2_status setup_resident(sp2_ctx c, const sp2::RunPlan& plan) {
   // cooperative | ordinary: FP64 N = 64 228 | 254 | 67, 300 312 | 321 | 107, FP32
   // N = 400 314 | 279 | 97; one thread, FP64 N = 64: 647 | 301 | 279. Larger runs
   // fill the device by themselves (FP64 N = 1000, 8 threads: 1236 | 917).
-  int members = 0;
-  for (const sp2::RunSeat& seat : plan.seats) members += seat.size > 0 ? 1 : 0;
-  c->run_members = (count == 1 && 2 * members <= c->num_cus) ? members : 0;
+  c->run_members = 0;
+  for (const sp2::RunSeat& seat : plan.seats) c->run_members += seat.size > 0 ? 1 : 0;
+  c->run_small = (count == 1 && 2 * c->run_members <= c->num_cus);
   SP2_HIP(c, pin(c, count * sizeof(DevState) + 256));
   c->h_inst = inst;
   c->mcweeny = false;
@@ -926,11 +928,19 @@ sp2_status run_persistent(sp2_ctx c) {
   return SP2_OK;
 }
 
-// One resident run: state reset, the launch, and the copy of the
-// states and the control words. A launch that was refused, and has run nothing,
-// clears c->teams_ok; so does one whose teams did not meet in time, whose
-// iterates and states the other driver forms anew from F.
-sp2_status run_resident(sp2_ctx c) {
+// Times that a run's gate may be shut in a process without cooperative
+// launches before it gives up.
+constexpr int kGateTries = 3;
+
+// One resident run: state reset, the launch, and the copy of the states and
+// the control words. The device gives cooperative launches to one process at
+// a time; where it refuses them, every run is an ordinary launch behind a gate
+// (whose workgroups are placed between two runs of the other process; in a
+// launch sequence each kernel waited for one: beside FP32 N = 3001 without a
+// pause, a run of that size took 150 ms, now 11, and the other 12). A run without room, which has done
+// nothing, clears c->teams_ok; so does one whose teams did not meet in time,
+// whose iterates and states the other driver forms anew from F.
+sp2_status run_resident(sp2_ctx c, int shut = 0) {
   const int count = static_cast<int>(c->hi.size());
   hipStream_t s = c->stream;
   int32_t* const err = reinterpret_cast<int32_t*>(c->d_st + count);
@@ -953,7 +963,7 @@ sp2_status run_resident(sp2_ctx c) {
   a.wait_limit = c->run_wait_ms * c->wall_khz;
   a.gate = err + 2;
   a.gate_limit = c->gate_ticks;
-  a.members = c->gate_ok ? c->run_members : 0;
+  a.members = (c->refused || (c->run_small && c->gate_ok)) ? c->run_members : 0;
   c->timed = false;
   c->square_ms.clear();
   c->norm_ms.clear();
@@ -965,6 +975,10 @@ sp2_status run_resident(sp2_ctx c) {
   if (launched == hipErrorIllegalState || launched == hipErrorNotSupported ||
       launched == hipErrorCooperativeLaunchTooLarge) {
     (void)hipGetLastError();
+    if (a.members == 0) {
+      c->refused = true;
+      return run_resident(c);
+    }
     c->teams_ok = false;
     return SP2_OK;
   }
@@ -976,8 +990,10 @@ sp2_status run_resident(sp2_ctx c) {
   SP2_HIP(c, hipStreamSynchronize(s));
   const int32_t* const word = reinterpret_cast<const int32_t*>(c->h_state + count);
   if (a.members > 0 && word[3] != sp2::kGateOpen) {
-    c->gate_ok = false;
-    return run_resident(c);   // as a cooperative launch
+    c->gate_ok = false;       // as a cooperative launch
+    if (shut + 1 < kGateTries) return run_resident(c, shut + 1);
+    c->teams_ok = false;
+    return SP2_OK;
   }
   float ms = 0.f;
   SP2_HIP(c, hipEventElapsedTime(&ms, c->ev_start, c->ev_stop));
