@@ -74,9 +74,13 @@ __device__ __forceinline__ void post(double* p, double v) {
 // dependent fused multiply-add a row where the pivots of sturm_below take a
 // division. A zero minor has the sign opposite to the one before it. Rows are
 // taken in blocks of eight, read from LDS ahead of their chain; rows past the
-// order (a = 2, b2 = 0) keep the sign, and a zero that follows a zero there
-// (x is an eigenvalue) counts nothing more. The minors shrink by at most some 2^-50
-// a row, so a rescale every block keeps them in range.
+// order (a = 2, b2 = 0, but kPadLink in the first) keep the sign. The link
+// gives a zero last minor (x is an eigenvalue) a successor of the sign it
+// counts as, where a chain of zeros would count one change a row; to a minor
+// that is not zero to within rounding it adds nothing. (The test for it in
+// the loop, on two zeros, took 0.7 us a Lanczos step.) The minors shrink by at
+// most some 2^-50 a row, so a rescale every block keeps them in range.
+constexpr double kPadLink = 0x1p-100;
 __device__ __forceinline__ int minors_below(const double* a, const double* b2, int blocks,
                                             double x) {
   double p0 = 0.0, p1 = 1.0;
@@ -102,7 +106,7 @@ __device__ __forceinline__ int minors_below(const double* a, const double* b2, i
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const double p2 = fma(d[e], p1, -b[e] * p0);
-      const bool ng = (p2 == 0.0) ? (p1 == 0.0) == neg : p2 < 0.0;
+      const bool ng = (p2 == 0.0) ? !neg : p2 < 0.0;
       cnt += (ng != neg) ? 1 : 0;
       neg = ng;
       p0 = p1;
@@ -144,7 +148,7 @@ __device__ __forceinline__ void ends(const double* ta, const double* tb, int m, 
   if (wave == 0) {
     sa[lane] = (lane < m) ? ta[lane] * is : 2.0;
     const double b = (lane > 0 && lane < m) ? tb[lane - 1] * is : 0.0;
-    sb[lane] = b * b;
+    sb[lane] = (lane == m) ? kPadLink : b * b;
   }
   __syncthreads();
   lo *= is;

@@ -62,7 +62,8 @@ int main() {
   };
   Scaled t;
   // eigenvalues 0 and 1
-  for (int i = 0; i < 64; ++i) t.a[i] = i < 2 ? 0.5 : 2.0, t.b2[i] = i == 1 ? 0.25 : 0.0;
+  for (int i = 0; i < 64; ++i)
+    t.a[i] = i < 2 ? 0.5 : 2.0, t.b2[i] = i == 1 ? 0.25 : (i == 2 ? kPadLink : 0.0);
   for (double x : {0.0, 1.0})
     if (minors_below(t.a, t.b2, 1, x) != (x == 0.0 ? 1 : 2))
       fail("2 x 2", 2, x, minors_below(t.a, t.b2, 1, x), x == 0.0 ? 1 : 2);
@@ -71,7 +72,7 @@ int main() {
     for (int i = 0; i < 64; ++i) {
       t.a[i] = i < m ? (static_cast<int>(g() % 9) - 4) / 8.0 : 2.0;
       const double b = (i > 0 && i < m) ? (1 + g() % 2) / 4.0 : 0.0;
-      t.b2[i] = b * b;
+      t.b2[i] = (i == m) ? kPadLink : b * b;
     }
     const double x = (static_cast<int>(g() % 17) - 8) / 8.0;
     const int got = minors_below(t.a, t.b2, (m + 7) / 8, x), want = reference(t, m, x);
@@ -90,7 +91,7 @@ int main() {
     for (int i = 0; i < 64; ++i) {
       t.a[i] = i < m ? u(g) - 0.5 : 2.0;
       const double b = (i > 0 && i < m) ? 0.25 * u(g) * (g() % 9 ? 1.0 : 1e-12) : 0.0;
-      t.b2[i] = b * b;
+      t.b2[i] = (i == m) ? kPadLink : b * b;
     }
     const double x = 2.0 * u(g) - 1.0;
     if (minors_below(t.a, t.b2, (m + 7) / 8, x) != pivots(t, m, x))
