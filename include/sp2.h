@@ -116,9 +116,12 @@ typedef enum {
 typedef enum {
   SP2_LAUNCH_AUTO = 0,       /* the library's choice. With the Frobenius norm
                                 and kernel_config, tail_split and
-                                kernel_timing 0, a resident run where the
-                                library's cost model finds it the faster
-                                driver: one launch for the whole run (a
+                                kernel_timing 0, a resident run for single
+                                instances of n <= 6144 (BF16x3: 3584) and for
+                                the batches for which it was measured to be
+                                the faster driver (by sizes, precision and
+                                method; few large or many small instances):
+                                one launch for the whole run (a
                                 cooperative one unless it is small; affine
                                 start, every step, the stop) in
                                 which each instance has a team of workgroups
@@ -488,7 +491,8 @@ sp2_status sp2_set_mcweeny(sp2_ctx ctx, int32_t count, const double* mu,
  * and n <= n_max[e] gives the 1-based configuration config_id[e]; instances
  * no entry covers use the library's built-in choice. count = 0 removes the
  * table. The table is copied; it applies to later sp2_init_dense and
- * sp2_batch_init calls on this context. Errors: SP2_INVALID_ARG (unknown
+ * sp2_batch_init calls on this context. A resident run (SP2_LAUNCH_AUTO) has
+ * square kernels of its own, which no table chooses. Errors: SP2_INVALID_ARG (unknown
  * configuration id or one whose precision differs from the entry's). */
 sp2_status sp2_set_kernel_table(sp2_ctx ctx, int32_t count,
                                 const int32_t* precision, const int64_t* n_max,

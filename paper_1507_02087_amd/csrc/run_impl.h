@@ -1,6 +1,7 @@
-// Resident runs: one cooperative launch computes a whole purification, from
-// the affine start to the stop, for every instance of the batch (included by
-// run_f64.hip, run_f32.hip and run_b3.hip).
+// Resident runs: one launch computes a whole purification, from the affine
+// start to the stop, for every instance of the batch (included by
+// run_f64.hip, run_f32.hip and run_b3.hip). Its workgroups wait for each other,
+// so it is a cooperative launch, or an ordinary one behind a gate (run_gate).
 //
 // What bounds a run of small or middle size is not the matrix cores but the
 // chain of launches of a step (square, tail reduction, scalar step: 20 us a
@@ -19,15 +20,17 @@
 //
 // Measured on one MI355X, us a step (launch sequence -> resident, floor = the
 // product at the rate of a large library product, 70 / 150 / 354 TFLOP/s):
-//   FP64  N = 100: 20.8 -> 10.0   1000: 61 -> 34 (14)   2500: 391 -> 286 (223)
-//         4096: 1122 -> 1101 (982)
-//   FP32  100: 23 -> 9.6   1000: 43 -> 24 (7)   1777: 99 -> 69 (37)
-//         3001: 290 -> 249 (180)   4000: 618 -> 528 (427)
-//   BF16x3  100: 23 -> 9.5   1000: 43 -> 22 (3)   2500: 99.7 -> 92.8 (44)
+//   FP64  N = 100: 20.3 -> 9.2   1000: 61 -> 35 (14)   2500: 391 -> 279 (223)
+//         4096: 1124 -> 1068 (982)
+//   FP32  100: 22.5 -> 9.2   1000: 42 -> 24 (7)   1777: 98 -> 70 (37)
+//         3001: 290 -> 248 (180)   4000: 618 -> 525 (427)
+//   BF16x3  100: 23 -> 9.1   1000: 43 -> 22 (3)   2500: 99 -> 92 (44)
 // What is left at small N is the meeting of a team (4.5 us: stores seen by
 // the other XCDs, the collection, the scalar step, the release) and the
 // latency of the first operands after it; at N >= 2000 the tiles of the last
 // round and the reduction and store of each tile (3 to 10 us, see plan_run).
+// Matrix cores busy over a whole run: FP64 N = 1000 40 %, FP32 1777 57 %, 3001
+// 69 %, 512 instances of 64 to 1024 rows 66 %, BF16x3 2500 (McWeeny) 23 %.
 #pragma once
 
 #include "square_impl.h"

@@ -8,8 +8,8 @@
 // configuration. The polynomial choices, the stop tests and the outcomes
 // live in device memory (one DevState per instance); the finalize kernel
 // counts stopped instances and tells the host, through host-coherent pinned
-// memory, when all have stopped. (A resident run is one cooperative launch
-// instead, see run_impl.h.) The host keeps up to kLookahead steps
+// memory, when all have stopped. (A resident run is one launch instead, see
+// run_impl.h.) The host keeps up to kLookahead steps
 // queued ahead of the step whose outcome it last observed, so the device
 // never waits on the host; steps queued after the stop return at once
 // because every kernel first reads its instance's done flag.
@@ -190,7 +190,7 @@ struct sp2_ctx_s {
   long long wall_khz = 100000;     // rate of the kernels' constant clock
   long long wait_ms = 2000;        // longest wait of a workgroup for an item
 
-  // resident run (one cooperative launch): the tile edge / 16, the seats of
+  // resident run (one launch): the tile edge / 16, the seats of
   // its workgroups, and the pinned host copy of the states
   bool resident = false;
   int run_mb = 0;

@@ -346,7 +346,7 @@ __host__ __device__ __forceinline__ size_t op_off(int row, int col, int ld) {
          ((row & 15) + 16 * ((col % KC) / V)) * V + col % V;
 }
 
-// Resident runs: one cooperative launch for a whole run. Each workgroup has
+// Resident runs: one launch for a whole run. Each workgroup has
 // a seat: its (first) instance, its rank in its team, the team's size
 // (0: the seat is empty), the team's first slot in the partial sums, and the
 // seat's tile in the last round when size does not divide the tiles (a tile
